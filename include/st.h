@@ -241,13 +241,10 @@ int st_check_edges(st_problem *p, int64_t E, const float *xa, const float *xb, u
 
 /* st_check_edges for callers that cannot allocate (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * check and results, with the pipeline's work lists in a fixed device array
- * of the library instead of buffers it allocates, so the call allocates
- * nothing (host or device).  E <= ST_NOALLOC_MAX_EDGES, else ST_EINVAL.  The
- * array (about 8.6 MB) is held on every device the call runs on until the
- * process ends; all calls on one device share it, so calls that overlap on a
- * device (different streams or threads) race and must be serialised by the
- * caller.  Inputs and outputs as for st_check_edges.  Async on stream. */
+ * check and results; the call allocates nothing (host or device) and keeps no
+ * work area, so calls on different streams or threads are independent.
+ * E <= ST_NOALLOC_MAX_EDGES, else ST_EINVAL.  Inputs and outputs as for
+ * st_check_edges.  Async on stream. */
 #define ST_NOALLOC_MAX_EDGES 65536
 int st_check_edges_noalloc(st_problem *p, int64_t E, const float *xa, const float *xb, uint8_t *free_out,
                            int32_t *first_hit, void *stream);
@@ -454,7 +451,8 @@ int st_proposal_set(st_problem *p, const float *z, float mix, void *stream);
 /* Launch shapes of the collision kernels: obstacles held in registers per
  * tile (4, 8 or 16, dividing the padded obstacle count; 0 keeps the current
  * value) and lanes per edge chunk for extension edges, bridge edges and
- * st_check_edges (powers of two up to 64; 0 keeps).  Results do not depend
+ * st_check_edges (powers of two up to 64; 0 keeps; choosing lanes for
+ * st_check_edges puts it on the chunked path, slower at every size measured).  Results do not depend
  * on these.  Synchronous; drops captured iteration graphs. */
 int st_set_tuning(st_problem *p, int32_t obstacle_tile, int32_t lanes_extension, int32_t lanes_bridge,
                   int32_t lanes_check);
@@ -464,18 +462,20 @@ int st_set_tuning(st_problem *p, int32_t obstacle_tile, int32_t lanes_extension,
  * the kinematic chain itself; shorter dependent chains for launches too small
  * to fill the device, more instructions per state) for extension edges,
  * bridge edges and st_check_edges; -1 chooses by launch size (4 up to 256
- * edges, else 1; a batch counts the edges of all its members); 0 keeps.  A translating robot always uses
+ * edges, else 1; a batch counts the edges of all its members; st_check_edges:
+ * the one-kernel path); 0 keeps.  A translating robot always uses
  * one lane per state.  Results do not depend on these.  Synchronous; drops
  * captured iteration graphs. */
 int st_set_state_split(st_problem *p, int32_t split_extension, int32_t split_bridge, int32_t split_check);
 
-/* Extension edges (at most ceil(sqrt(2) eta / h) + 1 states) are checked by a
- * flattened one-kernel path: a block of eight waves takes 4 x `edges_per_block`
- * consecutive edges (edges_per_block 1..8), lays their states end to end and
- * deals them to its waves in rounds of 64.
- * 0 selects the chunked path that bridges and st_check_edges use.  Results do
- * not depend on this.  Default 4.  In a batch (st_batch_create) a member on
- * the flattened path takes 8 (fewer, fuller blocks for many members).
+/* Extension edges (at most ceil(sqrt(2) eta / h) + 1 states) are checked by the
+ * one-kernel path that st_check_edges uses, with their steering: a block of
+ * eight waves takes 4 x `edges_per_block` consecutive edges (edges_per_block
+ * 1..8; fewer when the samples would not give every compute unit a block), lays
+ * their states end to end and deals them to its waves in rounds of 64.
+ * 0 selects the chunked path that long bridges use.  Results do not depend on
+ * this.  Default 4.  In a batch (st_batch_create) a member on this path takes
+ * 8 edges per block of four waves.
  * Synchronous; drops captured graphs. */
 int st_set_flat_extension(st_problem *p, int32_t edges_per_block);
 

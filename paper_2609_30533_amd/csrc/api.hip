@@ -166,17 +166,7 @@ static int build_scene(st_problem *p, const st_problem_desc *D) {
         sc.q_hi[j] = j < d ? (float)D->q_hi[j] : 0.f;
         sc.q_s[j] = j < d ? (float)D->q_start[j] : 0.f;
         sc.q_g[j] = j < d ? (float)D->q_goal[j] : 0.f;
-        sc.dh_ca[j] = 1.f;
     }
-    if (sc.kind == kDH)
-        for (int j = 0; j < d; ++j) {
-            const double *r = D->dh + 4 * j;
-            sc.dh_a[j] = (float)r[0];
-            sc.dh_ca[j] = (float)cos(r[1]);
-            sc.dh_sa[j] = (float)sin(r[1]);
-            sc.dh_d[j] = (float)r[2];
-            sc.dh_t0[j] = (float)r[3];
-        }
     // spheres sorted by link (stable)
     std::vector<int> ord(S);
     std::iota(ord.begin(), ord.end(), 0);
@@ -193,11 +183,13 @@ static int build_scene(st_problem *p, const st_problem_desc *D) {
         ro[o] = (float)D->obstacle_radius[o];
         if (ro[o] != sc.r_uni) sc.r_uni = -1.0f;
     }
-    for (int l = 0; l <= 8; ++l) {
+    // spheres of link l are [link_first[l], link_first[l + 1])
+    int link_first[10];
+    for (int l = 0; l <= 9; ++l) {
         int c = 0;
         for (int i = 0; i < S; ++i)
             if (D->sphere_link[ord[i]] < l) ++c;
-        sc.link_first[l] = c;
+        link_first[l] = c;
     }
     // do all obstacles share their waypoint times?
     bool shared = O > 0;
@@ -260,16 +252,60 @@ static int build_scene(st_problem *p, const st_problem_desc *D) {
         }
     }
     if (shared && O == 0) segt.assign(nseg + 1, INFINITY);
-    // LDS: segment table, spheres, waypoint times (generic mode), goal centres, boxes
+    // the image: segment table, spheres, waypoint times, goal centres, boxes, constants
     sc.lds_sph = sc.O_pad * nseg * 2;
     sc.lds_t = sc.lds_sph + S;
-    sc.lds_goal = sc.lds_t + (shared ? 0 : (int)((segt.size() + 3) / 4));
+    sc.lds_goal = sc.lds_t + (int)((segt.size() + 3) / 4);
     sc.lds_box = sc.lds_goal + S;
-    sc.lds_f4 = sc.lds_box + 4 * D->n_boxes;
-    // static geometry: link-pair masks and boxes as (axis, -axis . centre) rows
+    sc.lds_const = sc.lds_box + 4 * D->n_boxes;
+    sc.lds_f4 = sc.lds_const + const_f4(d);
     sc.n_box = D->n_boxes;
-    for (int k = 0; k < D->n_self_pairs; ++k) sc.self_mask[D->self_pairs[2 * k + 1]] |= 1u << D->self_pairs[2 * k];
+    sc.n_pair = D->n_self_pairs;
     sc.stat = (D->n_self_pairs > 0 || D->n_boxes > 0) ? 1 : 0;
+    unsigned self_mask[kMaxDof + 1] = {};
+    for (int k = 0; k < D->n_self_pairs; ++k) {
+        const int la = D->self_pairs[2 * k], lb = D->self_pairs[2 * k + 1];
+        self_mask[lb] |= 1u << la;
+        if ((unsigned)lb > ((sc.last_pair >> (4 * la)) & 15u))
+            sc.last_pair = (sc.last_pair & ~(15u << (4 * la))) | ((unsigned)lb << (4 * la));
+    }
+    std::vector<float4> image((size_t)sc.lds_f4, make_float4(0.f, 0.f, 0.f, 0.f));
+    std::copy(seg.begin(), seg.end(), image.begin());
+    std::copy(sph.begin(), sph.end(), image.begin() + sc.lds_sph);
+    memcpy(&image[sc.lds_t], segt.data(), segt.size() * sizeof(float));
+    for (int b = 0; b < D->n_boxes; ++b) {
+        const double *B = D->boxes + 15 * b;
+        float4 *row = &image[sc.lds_box + 4 * b];
+        for (int a = 0; a < 3; ++a) {
+            const double *u = B + 6 + 3 * a;
+            const double w = -(u[0] * B[0] + u[1] * B[1] + u[2] * B[2]);
+            row[a] = make_float4((float)u[0], (float)u[1], (float)u[2], (float)w);
+        }
+        row[3] = make_float4((float)B[3], (float)B[4], (float)B[5], 0.f);
+    }
+    // constants: the box (infinite in unused slots), then the link records
+    float4 *cst = &image[sc.lds_const];
+    {
+        float box[16];
+        for (int j = 0; j < 8; ++j) {
+            box[j] = j < d ? sc.q_lo[j] : -INFINITY;
+            box[8 + j] = j < d ? sc.q_hi[j] : INFINITY;
+        }
+        memcpy(cst, box, sizeof box);
+    }
+    auto as_float = [](int v) {
+        float f;
+        memcpy(&f, &v, sizeof f);
+        return f;
+    };
+    for (int l = 0; l <= d; ++l) {
+        float4 *rec = cst + kBoxRec + kLinkRec * l;
+        const double *r = sc.kind == kDH && l > 0 ? D->dh + 4 * (l - 1) : nullptr;
+        rec[0] = r ? make_float4((float)r[0], (float)cos(r[1]), (float)sin(r[1]), (float)r[2])
+                   : make_float4(0.f, 1.f, 0.f, 0.f);
+        rec[1] = make_float4(r ? (float)r[3] : 0.f, as_float(link_first[l]), as_float(link_first[l + 1]),
+                             as_float((int)self_mask[l]));
+    }
     // per-link bounding spheres of the broad phase: centroid of the link's
     // sphere centres, radius the farthest sphere surface, rounded outwards
     for (int l = 0; l <= d && l <= kMaxDof; ++l) {
@@ -291,45 +327,20 @@ static int build_scene(st_problem *p, const st_problem_desc *D) {
                                       (sp[2] - cf[2]) * (sp[2] - cf[2]));
                 rho = std::max(rho, e + sp[3]);
             }
-        sc.lbs[l] = make_float4(cf[0], cf[1], cf[2], (float)(rho * (1.0 + 1e-6) + 1e-6));
+        cst[kBoxRec + kLinkRec * l + 2] = make_float4(cf[0], cf[1], cf[2], (float)(rho * (1.0 + 1e-6) + 1e-6));
     }
+    // the documented limit covers the image without the constants and without
+    // waypoint times that all obstacles share
+    if ((size_t)(sc.lds_const - (shared ? sc.lds_goal - sc.lds_t : 0)) * sizeof(float4) > 64 * 1024)
+        return fail(ST_EINVAL, "obstacle table too large for LDS");
     int rc;
-    if ((rc = dev_upload(&p->d_sph, sph.data(), sph.size())) != ST_OK) return rc;
+    if ((rc = dev_upload(&p->d_image, image.data(), image.size())) != ST_OK) return rc;
     if ((rc = dev_upload(&p->d_ro, ro.data(), ro.size())) != ST_OK) return rc;
-    if ((rc = dev_upload(&p->d_seg, seg.data(), seg.size())) != ST_OK) return rc;
-    if ((rc = dev_upload(&p->d_segt, segt.data(), segt.size())) != ST_OK) return rc;
-    sc.sph = p->d_sph;
+    sc.image = p->d_image;
     sc.ro = p->d_ro;
-    sc.seg = p->d_seg;
-    sc.seg_t = p->d_segt;
-    // obstacle radii for the continuous check
-    {
-        std::vector<float> radii((size_t)std::max(O, 1), 0.f);
-        for (int o = 0; o < O; ++o) radii[o] = (float)D->obstacle_radius[o];
-        if ((rc = dev_upload(&p->d_obs_r, radii.data(), radii.size())) != ST_OK) return rc;
-        sc.obs_r = p->d_obs_r;
-    }
-    if (D->n_boxes > 0) {
-        std::vector<float4> bx((size_t)4 * D->n_boxes);
-        for (int b = 0; b < D->n_boxes; ++b) {
-            const double *B = D->boxes + 15 * b;
-            for (int a = 0; a < 3; ++a) {
-                const double *u = B + 6 + 3 * a;
-                const double w = -(u[0] * B[0] + u[1] * B[1] + u[2] * B[2]);
-                bx[4 * b + a] = make_float4((float)u[0], (float)u[1], (float)u[2], (float)w);
-            }
-            bx[4 * b + 3] = make_float4((float)B[3], (float)B[4], (float)B[5], 0.f);
-        }
-        if ((rc = dev_upload(&p->d_box, bx.data(), bx.size())) != ST_OK) return rc;
-        sc.box = p->d_box;
-    }
     // sphere centres at q_g for the goal-state tests
-    ST_HIP(hipMalloc((void **)&p->d_goal, std::max(S, 1) * sizeof(float4)));
-    sc.goal = nullptr;
-    ST_HIP(launch_goal_centers(sc, p->d_goal));
+    ST_HIP(launch_goal_centers(sc, p->d_image + sc.lds_goal));
     ST_HIP(hipDeviceSynchronize());
-    sc.goal = p->d_goal;
-    if (scene_lds_bytes(sc) > 64 * 1024) return fail(ST_EINVAL, "obstacle table too large for LDS");
     // the static terms at q_g, decided once by the state test itself with the
     // moving obstacles left out
     sc.goal_blocked = 0;
@@ -524,7 +535,7 @@ static void destroy(st_problem *p) {
     edge_bufs_free(p->ebufs);
     edge_bufs_free(p->ebufs_api);
     for (hipEvent_t ev : p->prof_ev) (void)hipEventDestroy(ev);
-    void *bufs[] = {p->d_sph, p->d_ro, p->d_seg, p->d_segt, p->d_goal, p->d_obs_r, p->d_box, p->d_gfree, p->d_wlo, p->d_whi, p->d_wcum,
+    void *bufs[] = {p->d_image, p->d_ro, p->d_gfree, p->d_wlo, p->d_whi, p->d_wcum,
                     p->tree.x, p->tree.parent, p->tree.cost, p->tree.rootT, p->d_plan};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
@@ -621,6 +632,7 @@ int st_set_tuning(st_problem *p, int32_t obstacle_tile, int32_t lanes_extension,
     p->tune_ext = se;
     p->tune_br = sb;
     p->tune_api = sk;
+    if (lanes_check != 0) p->api_lanes = true;
     ST_HIP(hipDeviceSynchronize());
     graphs_free(p);
     return ST_OK;
@@ -644,6 +656,7 @@ int st_set_state_split(st_problem *p, int32_t split_extension, int32_t split_bri
     p->split_ext = se;
     p->split_br = sb;
     p->split_api = sk;
+    if (split_check != 0) p->api_split = sk >= 0;
     ST_HIP(hipDeviceSynchronize());
     graphs_free(p);
     return ST_OK;
@@ -669,6 +682,11 @@ int st_check_edges(st_problem *p, int64_t E, const float *xa, const float *xb, u
                    int32_t *first_hit, void *stream) {
     if (!p || E < 0 || (E > 0 && (!xa || !xb || !free_out))) return fail(ST_EINVAL, "st_check_edges: bad arguments");
     if (E == 0) return ST_OK;
+    // the one-kernel check, unless the caller chose lanes for the chunked one
+    if (!p->api_lanes && !p->api_split) {
+        ST_HIP(launch_check_edges_flat(p->sc, E, xa, xb, free_out, first_hit, (hipStream_t)stream));
+        return ST_OK;
+    }
     // separate from the planner's buffers, which captured graphs refer to
     int rc = edge_bufs_reserve(p->ebufs_api, E);
     if (rc != ST_OK) return rc;

@@ -142,9 +142,7 @@ static int batch_build(st_batch *b) {
         scan_nn[m] = a.scan_nn;
         scan_br[m] = a.scan_br;
         steer[m] = a.steer;
-        // the batch's extension launch: the most edges per block (fewer, fuller
-        // blocks for its many members)
-        if (a.edge_ext.flat > 0) a.edge_ext.flat = kFlatEdges;
+        if (a.edge_ext.flat > 0) flat_shape_batch(a.edge_ext);
         edge_ext[m] = a.edge_ext;
         edge_br[m] = a.edge_br;
         ins[m] = a.insert;
@@ -199,7 +197,11 @@ static int batch_build(st_batch *b) {
             c.nb_sample = std::max(c.nb_sample, smp[m].nb);
             c.nb_items_ext = std::max(c.nb_items_ext, edge_ext[m].nb_items);
             c.nb_items_br = std::max(c.nb_items_br, edge_br[m].nb_items);
-            if (edge_ext[m].flat > 0) c.nb_flat = std::max(c.nb_flat, flat_blocks(edge_ext[m].E, edge_ext[m].flat));
+            if (edge_ext[m].flat > 0) {
+                c.nb_flat = std::max(c.nb_flat, (int)flat_blocks(edge_ext[m]));
+                c.lds_flat = flat_lds_bytes(edge_ext[m]);
+                c.flat_waves = edge_ext[m].flat_waves;
+            }
             c.nb_bcheck = std::max<int>(c.nb_bcheck, (int)b->mem[m]->prm.batch);  // one wave each
             c.lds = std::max(c.lds, scene_lds_bytes(b->mem[m]->sc));
             c.lds_sample = std::max(c.lds_sample, sample_lds_bytes(b->mem[m], nullptr));

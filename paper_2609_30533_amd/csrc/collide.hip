@@ -75,10 +75,10 @@ __global__ __launch_bounds__(256) void k_edge_continuous(SceneDev sc, int64_t E,
     float best = INFINITY;
     const float *lt = reinterpret_cast<const float *>(lds + sc.lds_t);
     for (int o = 0; o < sc.O; ++o) {
-        const int ka = sc.obs_mode == kObsShared ? shared_segment(sc, ta) : generic_segment(sc, lds, o, ta);
-        const int kb = sc.obs_mode == kObsShared ? shared_segment(sc, tb) : generic_segment(sc, lds, o, tb);
+        const int ka = sc.obs_mode == kObsShared ? shared_segment(sc, lds, ta) : generic_segment(sc, lds, o, ta);
+        const int kb = sc.obs_mode == kObsShared ? shared_segment(sc, lds, tb) : generic_segment(sc, lds, o, tb);
         for (int k = ka; k <= kb; ++k) {
-            const float tk1 = sc.obs_mode == kObsShared ? sc.seg_t[k + 1] : lt[o * (sc.n_seg + 1) + k + 1];
+            const float tk1 = lt[(sc.obs_mode == kObsShared ? 0 : o * (sc.n_seg + 1)) + k + 1];
             const float t0 = k == ka ? ta : lds[(o * sc.n_seg + k) * 2].w;
             const float t1 = k == kb ? tb : tk1;
             float c0x, c0y, c0z, c1x, c1y, c1z;
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) void k_edge_continuous(SceneDev sc, int64_t E,
                 const float pd = fmaf(p0x, dx, fmaf(p0y, dy, p0z * dz));
                 const float u = pp > 0.f ? fminf(fmaxf(-pd / pp, 0.f), 1.f) : 0.f;
                 const float mx = fmaf(u, dx, p0x), my = fmaf(u, dy, p0y), mz = fmaf(u, dz, p0z);
-                const float dist = sqrtf(fmaf(mx, mx, fmaf(my, my, mz * mz))) - (sp.w + sc.obs_r[o]);
+                const float dist = sqrtf(fmaf(mx, mx, fmaf(my, my, mz * mz))) - (sp.w + sc.ro[o]);
                 best = fminf(best, dist);
             }
         }
@@ -126,13 +126,18 @@ __global__ void k_goal_centers(SceneDev sc, float4 *out) {
 #pragma unroll
     for (int j = 0; j < kMaxDof; ++j) q[j] = sc.q_g[j];
     float cx, cy, cz, as;
+    const float4 sp = sc.image[sc.lds_sph + s];
     if (sc.kind == kTranslate) {
-        sphere_translate(sc, q, sc.sph[s], cx, cy, cz, as);
+        sphere_translate(sc, q, sp, cx, cy, cz, as);
     } else {
         Frame f;
         frame_identity(f);
-        for (int l = 1; l <= sc.d && sc.link_first[l] <= s; ++l) dh_compose(sc, l - 1, q[l - 1], f);
-        sphere_world(f, sc.sph[s], cx, cy, cz, as);
+        for (int l = 1; l <= sc.d; ++l) {
+            const LinkRec lk = link_rec(sc, sc.image, l);
+            if (lk.s0 > s) break;
+            dh_compose(lk, next_angle(q), f);
+        }
+        sphere_world(f, sp, cx, cy, cz, as);
     }
     out[s] = make_float4(cx, cy, cz, as);
 }
@@ -490,11 +495,34 @@ EdgeArgs edge_args(const SceneDev &sc, const EdgeBufs &eb, int64_t E, const floa
     const int64_t per_block = 4 * (int64_t)(64 >> lpe_shift);
     const int64_t want = (E + per_block - 1) / per_block;
     a.nb_items = (int)std::min<int64_t>(std::max<int64_t>(want, min_item_blocks), 8192);
-    a.flat = 0;
+    a.flat = a.flat_team = a.flat_waves = a.flat_w0 = 0;
     a.skip_finish = 0;
     return a;
 }
 
+
+template <int KIND, int OT, int OBS>
+__global__ __launch_bounds__(64 * kFlatWaves) void k_edge_flat(EdgeArgs a) {
+    extern __shared__ float4 lds[];
+    edge_flat_body<KIND, OT, OBS>(a, lds, blockIdx.x,
+                                  [&](int64_t e, float (&A)[kMaxDof + 1], float (&B)[kMaxDof + 1]) {
+                                      load_edge_rows(a.xa, a.xb, e, a.sc.d, A, B);
+                                      return true;
+                                  });
+}
+
+hipError_t launch_check_edges_flat(const SceneDev &sc, int64_t E, const float *xa, const float *xb, uint8_t *free_out,
+                                   int32_t *first_hit, hipStream_t s) {
+    if (E <= 0) return hipSuccess;
+    EdgeArgs a = edge_args(sc, EdgeBufs{}, E, xa, xb, nullptr, free_out, first_hit, 6, nullptr, 0, 0);
+    flat_shape_api(a);
+    const size_t lds = scene_lds_bytes(sc) + flat_lds_bytes(a);
+    dispatch_scene(sc, [&](auto kind, auto ot, auto obs) {
+        k_edge_flat<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value>
+            <<<dim3((unsigned)flat_blocks(a)), dim3(64 * a.flat_waves), lds, s>>>(a);
+    });
+    return hipGetLastError();
+}
 
 hipError_t launch_check_edges(const SceneDev &sc, const EdgeBufs &eb, int64_t E, const float *xa, const float *xb,
                               const uint8_t *valid, uint8_t *free_out, int32_t *first_hit, int lpe_shift,

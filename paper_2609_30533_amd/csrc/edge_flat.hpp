@@ -1,11 +1,17 @@
 // edge_flat.hpp -- edge-check building blocks shared by the collision
 // translation unit and the extension pipeline: endpoint rows, the state count
-// of a discretised edge, and the flattened check of short edges.
+// of a discretised edge, and the one-kernel edge check.
 #pragma once
+
+#include <algorithm>
 
 #include "st_internal.hpp"
 
 namespace st {
+
+// A space-time state in registers: the configuration in slots 0 .. d-1, zeros
+// up to slot kMaxDof - 1, the time in slot kMaxDof whatever d is (a slot that
+// depends on d would put the row into scratch memory).
 
 // Both endpoint rows of edge e (rows of d + 1 floats: configuration, then
 // time), earlier time first.  All the row loads are issued before the first
@@ -14,12 +20,14 @@ namespace st {
 __device__ __forceinline__ void load_edge_rows(const float *xa, const float *xb, int64_t e, int d,
                                                float (&A)[kMaxDof + 1], float (&B)[kMaxDof + 1]) {
     const float *pa = xa + e * (d + 1), *pb = xb + e * (d + 1);
+    A[kMaxDof] = pa[d];
+    B[kMaxDof] = pb[d];
 #pragma unroll
-    for (int j = 0; j <= kMaxDof; ++j) {
-        A[j] = j <= d ? pa[j] : 0.f;
-        B[j] = j <= d ? pb[j] : 0.f;
+    for (int j = 0; j < kMaxDof; ++j) {
+        A[j] = j < d ? pa[j] : 0.f;
+        B[j] = j < d ? pb[j] : 0.f;
     }
-    if (A[d] > B[d]) {
+    if (A[kMaxDof] > B[kMaxDof]) {
 #pragma unroll
         for (int j = 0; j <= kMaxDof; ++j) {
             const float tmp = A[j];
@@ -41,126 +49,172 @@ __device__ __forceinline__ int32_t edge_states(const float (&A)[kMaxDof + 1], co
             D2 += dq * dq;
         }
     }
-    const double span = fmax(sqrt(D2), v * ((double)B[d] - (double)A[d]));
+    const double span = fmax(sqrt(D2), v * ((double)B[kMaxDof] - (double)A[kMaxDof]));
     int64_t n = (int64_t)ceil(span / h);
     if (n < 1) n = 1;
     if (n > (1ll << 30)) n = 1ll << 30;
     return (int32_t)n;
 }
 
+// State j of an edge of n steps: the endpoint itself for j = n.
+__device__ __forceinline__ void edge_state(const float (&A)[kMaxDof + 1], const float (&B)[kMaxDof + 1], int32_t j,
+                                           int32_t n, float (&q)[kMaxDof], float &t) {
+    const float s = (float)j * (1.0f / (float)n);
+    const bool last = j == n;
+#pragma unroll
+    for (int k = 0; k < kMaxDof; ++k) q[k] = last ? B[k] : fmaf(s, B[k] - A[k], A[k]);
+    t = last ? B[kMaxDof] : fmaf(s, B[kMaxDof] - A[kMaxDof], A[kMaxDof]);
+}
+
 // ---------------------------------------------------------------------------
-// Short edges, flattened: a block of kFlatWaves waves takes kFlatGroups x
-// a.flat consecutive edges, lays their states end to end (edge after edge,
-// state order inside an edge) in rounds of 64, and decides them completely:
-// state count, checks, free / first hit and the work counters, in one kernel.
-// The rounds are dealt to the block's waves in turn (wave w takes rounds w,
-// w + kFlatWaves, ...), so the state checks spread evenly over the CU's SIMDs
-// (two waves each, so that one's memory waits overlap the other's arithmetic)
-// whatever the edges' lengths; the scene is staged into LDS once per block.
-// A lane skips a state above a hit already found for its edge (by any wave);
-// within a round the lanes of one edge form the group of the FIRST rule, and
-// hits merge with an atomic minimum, so the least colliding index is exact.
-// Meant for edges of bounded length (extensions).
+// Edge check in one kernel.  A team of waves takes G consecutive edges (G <=
+// 64) and decides them completely (state counts, checks, free / first hit,
+// work counters), in phases.  A phase checks the states [lo, lo + width) of
+// every edge of the team still without a hit, laid end to end and dealt to the
+// team's waves in rounds; the next phase starts behind them, wider.  A team is
+// one wave (no barrier after the scene is staged, and no wave waits for
+// another), or the whole block when a launch has fewer edges than the device
+// has SIMDs.
+//
+// Bound by VALU issue (a state check of the 6-DOF arm is about 3700
+// instructions, 2700 of them sphere pairs) and, with a round or two per wave,
+// by its dependent chain.  Most edges that collide do so within their first
+// states (two on average for random extensions of the 6-DOF arm, one for the
+// 7-DOF arm among 32 obstacles), and a lane that checks a state past its
+// edge's first hit is wasted, so the first phase is narrow; what survives it
+// is mostly free and needs all its states.  A round with fewer states than
+// lanes gives each state 2, 4 or 8 adjacent lanes that share its spheres out
+// (arms only), which shortens the chain of the narrow phases.
+//
+// A lane skips a state above a hit already found for its edge; within a round
+// the lanes of one edge form the group of the FIRST rule, and hits merge with
+// an atomic minimum; phases run in state order, so the least colliding index
+// is exact.
 // ---------------------------------------------------------------------------
 
-constexpr int kFlatEdges = 8;  // edges per wave at most (a.flat of them)
-constexpr int kFlatWaves = 8;  // waves per block (two per SIMD)
-constexpr int kFlatGroups = 4;  // the edges of a block: kFlatGroups x a.flat
-constexpr int kFlatBlockEdges = kFlatEdges * kFlatGroups;
+constexpr int kFlatMaxEdges = 64;  // edges per team at most (one per lane)
+constexpr int kFlatMaxShift = 3;   // lanes per state at most (log2)
+constexpr int kFlatMaxWidth = 4096;// states of one edge per phase at most
+constexpr int kFlatWaves = 8;      // waves per block at most
+
+// Dynamic LDS behind the scene: per team both endpoint rows, state counts and
+// least hits, per wave the edges that start in its round.
+inline __host__ __device__ int flat_team_f4(int G) { return 4 * G + (2 * G + 3) / 4; }
+inline size_t flat_lds_bytes(int waves, int team, int G) {
+    return (size_t)(waves / team) * flat_team_f4(G) * 16 + (size_t)waves * 64 * sizeof(int32_t);
+}
+
+// Inclusive scan over the wave's lanes in six cross-lane steps (row shifts,
+// then the rows' last lanes broadcast).
+template <class Op>
+__device__ __forceinline__ int wave_scan(int x, int identity, Op op) {
+    x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x111, 0xf, 0xf, false));  // row_shr:1
+    x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x112, 0xf, 0xf, false));  // row_shr:2
+    x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x114, 0xf, 0xf, false));  // row_shr:4
+    x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x118, 0xf, 0xf, false));  // row_shr:8
+    x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x142, 0xa, 0xf, false));  // row_bcast:15
+    x = op(x, __builtin_amdgcn_update_dpp(identity, x, 0x143, 0xc, 0xf, false));  // row_bcast:31
+    return x;
+}
+
+// Orders a wave's own LDS accesses across its lanes (they execute in order; this
+// keeps the compiler from moving or forwarding them).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 template <int KIND, int OT, int OBS, class Rows>
 __device__ __forceinline__ void edge_flat_body(const EdgeArgs &a, float4 *lds, int bx, Rows &&rows) {
-    __shared__ float s_A[kFlatBlockEdges][kMaxDof + 1], s_B[kFlatBlockEdges][kMaxDof + 1];
-    __shared__ int32_t s_off[kFlatBlockEdges + 1], s_n[kFlatBlockEdges], s_hit[kFlatBlockEdges];
     const SceneDev &sc = a.sc;
     const int d = sc.d;
-    const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
-    const int NE = a.flat * kFlatGroups;  // edges of this block
-    const int64_t e0 = (int64_t)bx * NE;
+    const int wv = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63, nwv = blockDim.x >> 6;
+    const int G = a.flat, TW = a.flat_team;  // edges and waves of a team
+    const int team = wv / TW, tw = wv - team * TW, teams = nwv / TW;
+    float4 *s_row = lds + sc.lds_f4 + team * flat_team_f4(G);  // edge i: A at [4 i], B at [4 i + 2]
+    int32_t *s_n = reinterpret_cast<int32_t *>(s_row + 4 * G), *s_hit = s_n + G;
+    int32_t *s_map = reinterpret_cast<int32_t *>(lds + sc.lds_f4 + teams * flat_team_f4(G)) + 64 * wv;
+    const int64_t e = ((int64_t)bx * teams + team) * G + lane;  // the lane's edge
     // the edges' rows first (rows(e, A, B) fills both endpoints, earlier
     // time first, and returns false for an edge not to check), so that the
     // producer's loads are in flight while other threads stage the scene;
     // the staging's barrier also publishes the rows
-    if (tid < kFlatBlockEdges) {
-        const int64_t e = e0 + tid;
-        int32_t n = -1;
-        if (tid < NE && e < a.E) {
+    int32_t n_own = -1;
+    if (tw == 0 && lane < G) {
+        if (e < a.E) {
             float A[kMaxDof + 1], B[kMaxDof + 1];
             if (rows(e, A, B)) {
-                n = edge_states(A, B, d, sc.v_d, sc.h_d);
-#pragma unroll
-                for (int j = 0; j <= kMaxDof; ++j) {
-                    s_A[tid][j] = A[j];
-                    s_B[tid][j] = B[j];
-                }
+                n_own = edge_states(A, B, d, sc.v_d, sc.h_d);
+                s_row[4 * lane] = make_float4(A[0], A[1], A[2], A[3]);
+                s_row[4 * lane + 1] = make_float4(A[4], A[5], A[6], A[7]);
+                s_row[4 * lane + 2] = make_float4(B[0], B[1], B[2], B[3]);
+                s_row[4 * lane + 3] = make_float4(B[4], B[5], B[6], B[7]);
             }
         }
-        s_n[tid] = n;
-        s_hit[tid] = kNoHit;
+        s_n[lane] = n_own;
+        s_hit[lane] = kNoHit;
     }
     stage_obstacles(sc, lds);
-    if (tid < 64) {
-        // exclusive prefix of the state counts (kFlatBlockEdges <= 64 lanes)
-        const int c = tid < kFlatBlockEdges ? (s_n[tid] >= 0 ? s_n[tid] + 1 : 0) : 0;
-        int incl = c;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += v;
+    if (tw != 0 && lane < G) n_own = s_n[lane];
+    int lo = 0, width = a.flat_w0;
+    int32_t hit_own;
+    for (;;) {
+        // the phase's states of the lane's edge and their place
+        hit_own = lane < G ? __atomic_load_n(&s_hit[lane], __ATOMIC_RELAXED) : 0;
+        const int left = n_own - lo + 1;  // (an edge not to check has n = -1)
+        const int c = lane < G && hit_own == kNoHit && left > 0 ? min(left, width) : 0;
+        const int incl = wave_scan(c, 0, [](int x, int y) { return x + y; });
+        const int off = incl - c, T = __builtin_amdgcn_readlane(incl, 63);
+        const int m = __popcll(__ballot(c > 0));
+        if (TW > 1) __syncthreads();  // no wave merges a hit before all have read them
+        if (T == 0) break;
+        // lanes per state: what the phase's states leave free
+        int shift = 0;
+        if (KIND != kTranslate)
+            while (shift < kFlatMaxShift && (T << (shift + 1)) <= 64 * TW) ++shift;
+        const int per = 64 >> shift, part = lane & ((1 << shift) - 1);
+        for (int base = tw * per; base < T; base += per * TW) {
+            // the edge of each state of the round: edges mark the slot they
+            // start in, a scan carries the mark on
+            s_map[lane] = -1;
+            wave_lds_fence();
+            if (c > 0 && off < base + per && off + c > base) s_map[max(off - base, 0)] = lane;
+            wave_lds_fence();
+            const int mark = wave_scan(s_map[lane], -1, [](int x, int y) { return max(x, y); });
+            const int i = __shfl(mark, lane >> shift, 64);
+            const int o0 = __shfl(off, i, 64);
+            const int32_t n = __shfl(n_own, i, 64);
+            const int g = base + (lane >> shift), j = lo + g - o0;
+            // a state above a known hit of its edge is not needed
+            const bool act = g < T && j <= __atomic_load_n(&s_hit[i], __ATOMIC_RELAXED);
+            // the lanes of lower states of this edge in this round (FIRST rule)
+            const uint64_t lower = ((1ull << (lane - part)) - 1ull) & ~((1ull << (max(o0 - base, 0) << shift)) - 1ull);
+            const float4 a0 = s_row[4 * i], a1 = s_row[4 * i + 1], b0 = s_row[4 * i + 2], b1 = s_row[4 * i + 3];
+            const float A[kMaxDof + 1] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+            const float B[kMaxDof + 1] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+            float q[kMaxDof];
+            float t;
+            edge_state(A, B, j, n, q, t);
+            const bool hit = state_hits<KIND, OT, OBS, true, KIND == kTranslate ? 1 : kSplitAny>(
+                sc, lds, q, t, act, 0ull, lower, part, shift);
+            if (hit && act && part == 0) atomicMin(&s_hit[i], j);
         }
-        if (tid < kFlatBlockEdges) s_off[tid] = incl - c;
-        if (tid == kFlatBlockEdges - 1) s_off[kFlatBlockEdges] = incl;
+        if (TW > 1) __syncthreads();
+        lo += width;
+        // at least four times as wide, and half a state per lane
+        width = min(kFlatMaxWidth, max(4 * width, 32 * TW / m));
     }
-    __syncthreads();
-    const int total = s_off[kFlatBlockEdges];
-    for (int base = wv * 64; base < total; base += 64 * kFlatWaves) {
-        const int g = base + lane;
-        // edge of state g: the number of edge starts at or below g, minus one
-        int i = 0;
-        for (int k = 1; k < kFlatBlockEdges; ++k) i += g >= s_off[k] ? 1 : 0;
-        const int j = g - s_off[i];
-        const int32_t n = s_n[i];
-        // a state above a known hit of its edge is not needed
-        const bool act = g < total && j <= __atomic_load_n(&s_hit[i], __ATOMIC_RELAXED);
-        // lanes of this edge in this round: its group for the FIRST rule
-        const int lo = max(s_off[i] - base, 0), hi = min(s_off[i + 1] - base, 64);
-        const uint64_t seg = (hi >= 64 ? ~0ull : ((1ull << hi) - 1ull)) & ~((1ull << lo) - 1ull);
-        const uint64_t lower = seg & ((1ull << lane) - 1ull);
-        float q[kMaxDof];
-        float t = 0.f;
-        if (act && j == n) {
-            // the last state is the endpoint itself
-#pragma unroll
-            for (int k = 0; k < kMaxDof; ++k) q[k] = k < d ? s_B[i][k] : 0.f;
-            t = s_B[i][d];
-        } else if (act) {
-            const float sj = (float)j * (1.0f / (float)n);
-#pragma unroll
-            for (int k = 0; k < kMaxDof; ++k) q[k] = k < d ? fmaf(sj, s_B[i][k] - s_A[i][k], s_A[i][k]) : 0.f;
-            t = fmaf(sj, s_B[i][d] - s_A[i][d], s_A[i][d]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < kMaxDof; ++k) q[k] = 0.f;
-        }
-        const bool hit = state_hits<KIND, OT, OBS, true>(sc, lds, q, t, act, seg, lower);
-        if (hit && act) atomicMin(&s_hit[i], j);
-    }
-    __syncthreads();
     // results and work counters
+    if (tw != 0) return;
     unsigned long long states = 0, edges = 0;
-    if (tid < NE && tid < kFlatBlockEdges) {
-        const int64_t e = e0 + tid;
-        const int32_t n = s_n[tid];
-        if (e < a.E && n >= 0) {
-            const int32_t h = s_hit[tid];
-            const bool fr = h == kNoHit;
-            a.free_out[e] = fr ? 1 : 0;
-            if (a.first_hit) a.first_hit[e] = fr ? -1 : h;
-            states = fr ? (unsigned long long)n + 1ull : (unsigned long long)h + 1ull;
-            edges = 1;
-        }
+    if (lane < G && e < a.E && n_own >= 0) {
+        const bool fr = hit_own == kNoHit;
+        a.free_out[e] = fr ? 1 : 0;
+        if (a.first_hit) a.first_hit[e] = fr ? -1 : hit_own;
+        states = fr ? (unsigned long long)n_own + 1ull : (unsigned long long)hit_own + 1ull;
+        edges = 1;
     }
-    if (a.work && wv == 0) {
+    if (a.work) {
         for (int o = 32; o > 0; o >>= 1) {
             states += __shfl_down(states, o, 64);
             edges += __shfl_down(edges, o, 64);
@@ -172,11 +226,46 @@ __device__ __forceinline__ void edge_flat_body(const EdgeArgs &a, float4 *lds, i
     }
 }
 
-
-// Blocks of the flattened path for E edges.
-inline int flat_blocks(int64_t E, int edges_per_block) {
-    const int64_t per = (int64_t)edges_per_block * kFlatGroups;
-    return (int)((E + per - 1) / per);
+// Launch shapes of the one-kernel check.  `w0` states per wave in the first
+// phase, shared out among the team's edges.
+inline void flat_set(EdgeArgs &a, int G, int team, int waves, int w0) {
+    a.flat = G;
+    a.flat_team = team;
+    a.flat_waves = waves;
+    a.flat_w0 = std::min(kFlatMaxWidth, std::max(1, w0 * team / G));
 }
+
+// st_check_edges: a wave takes one edge from 1025 edges on (the device has 1024
+// SIMDs), more as the launch grows (E / 3072, up to 32); below that 2, 4 or 8
+// waves share an edge.  100 bridge-length edges of the 6-DOF arm: 12.8 us with
+// eight waves per edge, 16.5 with one, 30 for the chunked plan / items / finish
+// kernels; 4096 extension edges: 24.5 us with 2 edges per wave, 34 with 8, 39
+// chunked; 262144 bridge-length edges of the 7-DOF arm: 665 us with 32 edges,
+// 740 with 8, 2970 chunked.
+inline void flat_shape_api(EdgeArgs &a) {
+    const int team = a.E <= 256 ? 8 : (a.E <= 512 ? 4 : (a.E <= 1024 ? 2 : 1));
+    const int G = (int)std::max<int64_t>(1, std::min<int64_t>(32, (a.E + 3071) / 3072));
+    flat_set(a, G, team, team == 1 ? 4 : team, 64);
+}
+
+// Extension edges of one problem: 4 x `number` edges (16 by default) per block
+// of eight waves, all their states in the first phase (at 4096 samples 98 us
+// per iteration of the 6-DOF arm; 102 with a first phase of four states per
+// edge, 126 with a wave per 4 edges, whose steering then has four lanes in use),
+// fewer edges when the samples would not give every CU a block.
+inline void flat_shape_extension(EdgeArgs &a, int number) {
+    flat_set(a, (int)std::max<int64_t>(1, std::min<int64_t>(4 * number, (a.E + 255) / 256)), 8, 8, 128);
+}
+
+// Extension edges of a batch member: 8 edges per block of four waves (the
+// mixed batch of 128 problems: 378 us per iteration; 404 with 32 edges and
+// eight waves, 438 with a wave per 8 edges).
+inline void flat_shape_batch(EdgeArgs &a) { flat_set(a, 8, 4, 4, 64); }
+
+inline int64_t flat_blocks(const EdgeArgs &a) {
+    const int64_t per = (int64_t)a.flat * (a.flat_waves / a.flat_team);
+    return (a.E + per - 1) / per;
+}
+inline size_t flat_lds_bytes(const EdgeArgs &a) { return flat_lds_bytes(a.flat_waves, a.flat_team, a.flat); }
 
 }  // namespace st

@@ -613,7 +613,7 @@ __device__ __forceinline__ bool steer_worker(const SteerArgs &a, int64_t w, floa
     float xr[kMaxDof + 1];
 #pragma unroll
     for (int j = 0; j < kMaxDof; ++j) xr[j] = j < d ? a.s.qr[(int64_t)j * a.B + w] : 0.f;
-    xr[d] = a.s.tr[w];
+    xr[kMaxDof] = a.s.tr[w];
     // a backward worker must name an existing group / slot
     const bool skip = (f & ST_FLAG_SKIP) || (dir != 0 && (g < 0 || g >= a.tree.n_pools - 1));
     const bool virt = a.variant == ST_INTERVAL_ROOT && dir == 1 && (f & ST_FLAG_USE_NEW);
@@ -622,34 +622,41 @@ __device__ __forceinline__ bool steer_worker(const SteerArgs &a, int64_t w, floa
     int32_t idx = -1;
     float cost0 = 0.f, root0 = 0.f;
     if (ok && virt) {
-        for (int j = 0; j < d; ++j) xn[j] = sc.q_g[j];
-        xn[d] = Tw;
+#pragma unroll
+        for (int j = 0; j < kMaxDof; ++j) xn[j] = j < d ? sc.q_g[j] : 0.f;
+        xn[kMaxDof] = Tw;
         root0 = Tw;
     } else if (ok) {
         idx = (int32_t)(key & 0xffffffffu);
-        for (int j = 0; j <= d; ++j) xn[j] = a.tree.x[(int64_t)j * a.tree.total + idx];
+#pragma unroll
+        for (int j = 0; j < kMaxDof; ++j) xn[j] = j < d ? a.tree.x[(int64_t)j * a.tree.total + idx] : 0.f;
+        xn[kMaxDof] = a.tree.x[(int64_t)d * a.tree.total + idx];
         cost0 = a.tree.cost[idx];
         root0 = dir == 0 ? 0.f : a.tree.rootT[idx];
     }
     float step = 0.f;
     if (ok) {
+        // (slots past d hold zeros on both sides and add exact zeros)
         const float sigma = dir == 0 ? 1.f : -1.f;
         float D2 = 0.f;
-        for (int j = 0; j < d; ++j) {
+#pragma unroll
+        for (int j = 0; j < kMaxDof; ++j) {
             const float e = xr[j] - xn[j];
             D2 = fmaf(e, e, D2);
         }
         if (a.variant == ST_INTERVAL_ROOT) {
-            const float vd = sigma * sc.v * (xr[d] - xn[d]);
+            const float vd = sigma * sc.v * (xr[kMaxDof] - xn[kMaxDof]);
             const float w2 = vd * fabsf(vd);
             if (!(D2 <= w2 && w2 > 0.f)) {
                 ok = false;  // rho infinite
             } else {
                 const float rho = sqrtf(0.5f * (D2 + w2));
                 const float alpha = fminf(1.f, a.eta / rho);  // Alg. 1: same fraction in q and t
-                for (int j = 0; j <= d; ++j) xnew[j] = fmaf(alpha, xr[j] - xn[j], xn[j]);
+#pragma unroll
+                for (int j = 0; j <= kMaxDof; ++j) xnew[j] = fmaf(alpha, xr[j] - xn[j], xn[j]);
                 float s2 = 0.f;
-                for (int j = 0; j < d; ++j) {
+#pragma unroll
+                for (int j = 0; j < kMaxDof; ++j) {
                     const float e = xnew[j] - xn[j];
                     s2 = fmaf(e, e, s2);
                 }
@@ -662,26 +669,32 @@ __device__ __forceinline__ bool steer_worker(const SteerArgs &a, int64_t w, floa
             } else {
                 const float fr = fminf(1.f, a.eta / D);
                 float s2 = 0.f;
-                for (int j = 0; j < d; ++j) {
+#pragma unroll
+                for (int j = 0; j < kMaxDof; ++j) {
                     xnew[j] = fmaf(fr, xr[j] - xn[j], xn[j]);
                     const float e = xnew[j] - xn[j];
                     s2 = fmaf(e, e, s2);
                 }
                 step = sqrtf(s2);
-                xnew[d] = xn[d] + sigma * step / sc.v;  // Eq. 8: maximum-speed timing
+                xnew[kMaxDof] = xn[kMaxDof] + sigma * step / sc.v;  // Eq. 8: maximum-speed timing
             }
         }
-        if (ok && !(xnew[d] >= 0.f && xnew[d] <= sc.H)) ok = false;  // leaves [0, H]
+        if (ok && !(xnew[kMaxDof] >= 0.f && xnew[kMaxDof] <= sc.H)) ok = false;  // leaves [0, H]
     }
     k.status[w] = status;
     k.new_idx[w] = -1;
     k.edge_valid[w] = ok ? 1 : 0;
     k.parent[w] = ok ? idx : -1;
     if (!ok) return false;
-    for (int j = 0; j <= d; ++j) {
-        k.xn[w * W + j] = xn[j];
-        k.xnew[w * W + j] = xnew[j];
+#pragma unroll
+    for (int j = 0; j < kMaxDof; ++j) {
+        if (j < d) {
+            k.xn[w * W + j] = xn[j];
+            k.xnew[w * W + j] = xnew[j];
+        }
     }
+    k.xn[w * W + d] = xn[kMaxDof];
+    k.xnew[w * W + d] = xnew[kMaxDof];
     k.cost_new[w] = cost0 + step;
     k.rootT_new[w] = root0;
     return true;
@@ -701,16 +714,15 @@ __global__ __launch_bounds__(256) void k_steer(SteerArgs a0, const SteerArgs *__
 // the resulting edges (a4), with no round trip through a separate launch.
 template <int KIND, int OT, int OBS>
 __device__ __forceinline__ void steer_flat_body(const SteerArgs &sa, const EdgeArgs &ea, float4 *lds, int bx) {
-    const int d = sa.sc.d;
     edge_flat_body<KIND, OT, OBS>(ea, lds, bx, [&](int64_t e, float (&A)[kMaxDof + 1], float (&B)[kMaxDof + 1]) {
         float xn[kMaxDof + 1], xnew[kMaxDof + 1];
         if (!steer_worker(sa, e, xn, xnew)) return false;
         // both endpoints, earlier time first
-        const bool sw = xn[d] > xnew[d];
+        const bool sw = xn[kMaxDof] > xnew[kMaxDof];
 #pragma unroll
         for (int j = 0; j <= kMaxDof; ++j) {
-            A[j] = j <= d ? (sw ? xnew[j] : xn[j]) : 0.f;
-            B[j] = j <= d ? (sw ? xn[j] : xnew[j]) : 0.f;
+            A[j] = sw ? xnew[j] : xn[j];
+            B[j] = sw ? xn[j] : xnew[j];
         }
         return true;
     });
@@ -729,7 +741,7 @@ __global__ __launch_bounds__(64 * kFlatWaves) void k_steer_flat_multi(const Stee
     extern __shared__ float4 lds[];
     const int m = members[blockIdx.y];
     const EdgeArgs &ea = ev[m];
-    if ((int64_t)blockIdx.x * kFlatGroups * ea.flat >= ea.E) return;
+    if ((int64_t)blockIdx.x * ea.flat * (ea.flat_waves / ea.flat_team) >= ea.E) return;
     steer_flat_body<KIND, OT, OBS>(sv[m], ea, lds, blockIdx.x);
 }
 
@@ -980,10 +992,12 @@ __global__ __launch_bounds__(256) void k_bridge_check(BridgeArgs a0, EdgeArgs ea
     float up = 0.f, cp = 0.f, cb = 0.f;
     if (has) {
 #pragma unroll
-        for (int j = 0; j <= kMaxDof; ++j) {
-            y[j] = j <= d ? a.tree.x[(int64_t)j * a.tree.total + bi] : 0.f;
-            xn[j] = j <= d ? k.xnew[w * W + j] : 0.f;
+        for (int j = 0; j < kMaxDof; ++j) {
+            y[j] = j < d ? a.tree.x[(int64_t)j * a.tree.total + bi] : 0.f;
+            xn[j] = j < d ? k.xnew[w * W + j] : 0.f;
         }
+        y[kMaxDof] = a.tree.x[(int64_t)d * a.tree.total + bi];
+        xn[kMaxDof] = k.xnew[w * W + d];
         up = a.dir[w] == 0 ? a.tree.rootT[bi] : k.rootT_new[w];
         cp = k.cost_new[w];
         cb = a.tree.cost[bi];
@@ -1010,8 +1024,9 @@ __global__ __launch_bounds__(256) void k_bridge_check(BridgeArgs a0, EdgeArgs ea
     }
     if (lane == 0) {
 #pragma unroll
-        for (int j = 0; j <= kMaxDof; ++j)
-            if (j <= d) k.xb[w * W + j] = y[j];
+        for (int j = 0; j < kMaxDof; ++j)
+            if (j < d) k.xb[w * W + j] = y[j];
+        k.xb[w * W + d] = y[kMaxDof];
         k.bridge[w] = (int32_t)bi;
         k.br_valid[w] = 1;
         k.Up[w] = up;
@@ -1019,7 +1034,7 @@ __global__ __launch_bounds__(256) void k_bridge_check(BridgeArgs a0, EdgeArgs ea
     }
     // the edge (x_new, y), earlier time first, and its state count
     float A[kMaxDof + 1], B[kMaxDof + 1];
-    const bool sw = xn[d] > y[d];
+    const bool sw = xn[kMaxDof] > y[kMaxDof];
 #pragma unroll
     for (int j = 0; j <= kMaxDof; ++j) {
         A[j] = sw ? y[j] : xn[j];
@@ -1029,15 +1044,8 @@ __global__ __launch_bounds__(256) void k_bridge_check(BridgeArgs a0, EdgeArgs ea
     const bool act = lane <= n;
     float q[kMaxDof];
     float t = 0.f;
-    if (act && lane == n) {
-#pragma unroll
-        for (int j = 0; j < kMaxDof; ++j) q[j] = j < d ? B[j] : 0.f;
-        t = B[d];
-    } else if (act) {
-        const float sj = (float)lane * (1.0f / (float)n);
-#pragma unroll
-        for (int j = 0; j < kMaxDof; ++j) q[j] = j < d ? fmaf(sj, B[j] - A[j], A[j]) : 0.f;
-        t = fmaf(sj, B[d] - A[d], A[d]);
+    if (act) {
+        edge_state(A, B, lane, n, q, t);
     } else {
 #pragma unroll
         for (int j = 0; j < kMaxDof; ++j) q[j] = 0.f;
@@ -1647,7 +1655,7 @@ void make_iter_args(const st_problem *p, int64_t B, const st_samples &in, const 
                            split_for(p->split_ext, launch_edges));
     // extension edges are short (rho <= eta: at most ceil(sqrt(2) eta / h) + 1
     // states): the flattened path, unless eta / h is unusually large
-    a.edge_ext.flat = std::sqrt(2.0) * p->prm.eta / p->prm.h <= 4096.0 ? p->flat_ext : 0;
+    if (p->flat_ext > 0 && std::sqrt(2.0) * p->prm.eta / p->prm.h <= 4096.0) flat_shape_extension(a.edge_ext, p->flat_ext);
     // insertion (a5)
     InsertArgs &ia = a.insert;
     ia.sc = p->sc;
@@ -1737,8 +1745,8 @@ int extend_batch(st_problem *p, int64_t B, const st_samples &in, const st_extend
         const EdgeArgs &ea = a.edge_ext;
         dispatch_scene_edges(p->sc, [&](auto kind, auto ot, auto obs) {
             k_steer_flat<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value>
-                <<<dim3(flat_blocks(ea.E, ea.flat)), dim3(64 * kFlatWaves), scene_lds_bytes(p->sc), s>>>(a.steer,
-                                                                                                          ea);
+                <<<dim3((unsigned)flat_blocks(ea)), dim3(64 * ea.flat_waves), scene_lds_bytes(p->sc) + flat_lds_bytes(ea),
+                   s>>>(a.steer, ea);
         });
         ST_HIP(hipGetLastError());
     } else {
@@ -1804,7 +1812,8 @@ int launch_batch_iteration(const BatchLaunch &L, hipStream_t s) {
         for (const BatchClass &c : L.classes) {
             dispatch_scene_edges(c.key, [&](auto kind, auto ot, auto obs) {
                 k_steer_flat_multi<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value>
-                    <<<dim3(c.nb_flat, c.n), dim3(64 * kFlatWaves), c.lds, s>>>(L.steer, L.edge_ext, c.members);
+                    <<<dim3(c.nb_flat, c.n), dim3(64 * c.flat_waves), c.lds + c.lds_flat, s>>>(
+                        L.steer, L.edge_ext, c.members);
             });
             ST_HIP(hipGetLastError());
         }

@@ -139,6 +139,8 @@ struct BatchClass {
     int n;                  // members
     int nb_sample, nb_items_ext, nb_items_br, nb_flat, nb_bcheck;  // grid maxima over the members
     size_t lds;             // dynamic LDS, maximum over the members
+    size_t lds_flat;        // the extension check's, behind the scene
+    int flat_waves;         // and its waves per block (the same for every member)
     size_t lds_sample;      // the sampler's (scene and guided windows), maximum over the members
 };
 

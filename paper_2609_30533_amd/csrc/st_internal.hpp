@@ -120,7 +120,9 @@ struct EdgeArgs {
     int32_t split_shift;        // lanes per state = 1 << split_shift
     int32_t nb_edge;            // blocks of the per-edge kernels
     int32_t nb_items;           // blocks of the item kernel
-    int32_t flat;               // > 0: short edges, flattened one-kernel path, this many per block
+    // one-kernel path: edges per team (0: chunked path), waves per team and per
+    // block, width of the first phase
+    int32_t flat, flat_team, flat_waves, flat_w0;
     int32_t skip_finish;        // 1: the consumer of the results does the finish step itself
 };
 
@@ -166,13 +168,8 @@ struct st_problem {
     std::vector<double> q_lo, q_hi, q_s, q_g;
     double t_min = 0, t_max = 0, v_max = 0, Lg = 0, L = 0;
     st::SceneDev sc{};
-    float4 *d_sph = nullptr;
+    float4 *d_image = nullptr; // the scene as staged into LDS
     float *d_ro = nullptr;     // obstacle radii [O_pad]
-    float4 *d_seg = nullptr;
-    float4 *d_goal = nullptr;  // sphere centres at q_g
-    float *d_obs_r = nullptr;  // obstacle radii
-    float4 *d_box = nullptr;   // static boxes, 4 rows each
-    float *d_segt = nullptr;
     // goal grid and windows
     int64_t k_lo = 0, k_hi = -1;
     uint8_t *d_gfree = nullptr;
@@ -194,7 +191,9 @@ struct st_problem {
     int tune_ext = 5, tune_br = 4, tune_api = 5;
     // lanes per state (log2) for the same three launches; -1 chooses by size
     int split_ext = -1, split_br = -1, split_api = -1;
-    // extension edges per block of the flattened path (0: chunked item path)
+    // st_check_edges takes the chunked path when the caller chose its lanes
+    bool api_lanes = false, api_split = false;
+    // a quarter of the extension edges per block of the one-kernel path (0: chunked item path)
     int flat_ext = 4;
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     int64_t graph_B = 0;
@@ -218,6 +217,9 @@ hipError_t launch_goal_centers(const SceneDev &sc, float4 *out);
 hipError_t launch_check_states(const SceneDev &sc, int64_t M, const float *x, uint8_t *free_out, hipStream_t s);
 int edge_bufs_reserve(EdgeBufs &eb, int64_t E);
 void edge_bufs_free(EdgeBufs &eb);
+// The check in one kernel (no work buffers); first_hit may be null.
+hipError_t launch_check_edges_flat(const SceneDev &sc, int64_t E, const float *xa, const float *xb, uint8_t *free_out,
+                                   int32_t *first_hit, hipStream_t s);
 // Lanes per chunk = 1 << lpe_shift (1..64).  first_hit and work may be null.
 hipError_t launch_check_edges(const SceneDev &sc, const EdgeBufs &eb, int64_t E, const float *xa, const float *xb,
                               const uint8_t *valid, uint8_t *free_out, int32_t *first_hit, int lpe_shift,
