@@ -361,6 +361,205 @@ enum { kScanRho = 0, kScanConfig = 1, kScanBridge = 2 };
 constexpr int kMinSliceNodes = 64;  // nearest-node scans: nodes per slice at least
 
 
+// ---------------------------------------------------------------------------
+// Large node sets: matrix-core filter, exact test of what passes it.
+//
+// The plain scan below is bound by VALU issue (about 20 instructions per pair,
+// 16 of them |x - q|^2).  Here a wave takes 64 queries and 32 nodes at a time:
+// two v_mfma_f32_32x32x16_bf16 per 32 queries give, for every pair, a lower
+// bound of |x - q|^2 minus the query's present bound, and 0.5 (configuration
+// distance) or 3.5 (rho) VALU instructions per pair tell whether any pair of
+// the tile can still improve its query.  Only those pairs are evaluated, with
+// the plain scan's own arithmetic, so the results are the same bit for bit.
+//
+// Bound.  With x = xh + xl + r, xh = bf16(x), xl = bf16(x - xh) and |r| <=
+// 2^-18 |x|, the sum  |x|^2 + |q|^2 - 2 (qh xh + qh xl + ql xh)  in FP32 differs
+// from |x - q|^2 by less than 2^-15.7 (|x|^2 + |q|^2): 3 2^-18 2 |x||q| from the
+// products left out and 27 additions of partial sums below 2 (|x|^2 + |q|^2).
+// Using (1 - eps) |x|^2 and (1 - eps) |q|^2, eps = 2^-14, makes it a lower bound.
+// The squares travel as three bf16 parts each, so one operand row is 27 of 32
+// places: 3 per coordinate, 3 for the node's square, 3 for the query's constant
+// (which multiply ones).  rho (Eq. 7) asks for D2 <= w2 and D2 + w2 <= best with
+// w2 = vd |vd|, vd = v sigma (t_q - t); with h = best / 2 that is
+//   D2 - h + |w2 - h| <= 0,
+// with 2^-17 h of slack for the constant's rounding.  Values that leave this
+// arithmetic (squares from 1e30 on) always pass the filter.
+//
+// Every slice first tests 32 of its nodes exactly and exchanges the queries'
+// bests with the other slices through the global keys then and at its second
+// and fifth round of 256 nodes.  An exchange is an atomic per query and slice
+// at the memory side, some 20 us for 4096 queries and 48 slices, so it is not
+// made every round (134 us instead of 101); without it every other tile passes
+// (129 us).  Measured, 4096 queries of 100003 nodes: rho 206 us plain, 101 so;
+// configuration distance 162 and 63.
+// ---------------------------------------------------------------------------
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int kFilterSeed = 32;          // nodes of a slice tested exactly first
+constexpr int kFilterSlice = 512;        // nodes per slice at least
+constexpr int kFilterBlocks = 768;       // blocks at most: three of four waves per CU
+constexpr int kFilterMinQueries = 24;    // tiles with fewer queries take the plain scan
+// ... and so do sets with fewer pairs of a node and a query.  4096 queries: 32768
+// nodes rho 73 us plain, 54 filtered; 16384 nodes 40 and 44; 1000 queries of 100000
+// nodes 57 and 70 (few tiles, so short slices or few blocks); configuration distance
+// 2048 x 65536 59 and 36.
+constexpr int64_t kFilterMinPairs = 1ll << 27;
+constexpr float kFilterEps = 1.0f / 16384.0f;   // 2^-14
+constexpr float kFilterSlack = 1.0f / 131072.0f; // 2^-17
+constexpr float kFilterMax = 1e30f;
+constexpr float kFilterPass = -1.7014118e38f;    // -2^127: passes whatever is added
+
+// x in three bf16 parts (24 bits).
+__device__ __forceinline__ void split3(float x, __bf16 &h, __bf16 &m, __bf16 &l) {
+    h = (__bf16)x;
+    const float r = x - (float)h;
+    m = (__bf16)r;
+    l = (__bf16)(r - (float)m);
+}
+
+// Places 8 c .. 8 c + 7 of a node's operand row (x: 7 coordinates, zeros past
+// d): place 3 j is xh_j, 3 j + 1 is xl_j, 3 j + 2 is xh_j again; 21 .. 23 the
+// square's parts.
+__device__ __forceinline__ void filter_node(const float (&x)[8], bool used, bf16x8 (&op)[3]) {
+    __bf16 v[24];
+    float n2 = 0.f;
+#pragma unroll
+    for (int j = 0; j < kMaxDof; ++j) n2 = fmaf(x[j], x[j], n2);
+    const bool plain = n2 < kFilterMax;  // (false for NaN)
+    // an unused row never passes
+    n2 = used ? (plain ? n2 * (1.0f - kFilterEps) : kFilterPass) : kFilterMax;
+#pragma unroll
+    for (int j = 0; j < kMaxDof; ++j) {
+        const float c = used && plain ? x[j] : 0.f;
+        const __bf16 h = (__bf16)c;
+        v[3 * j] = h;
+        v[3 * j + 1] = (__bf16)(c - (float)h);
+        v[3 * j + 2] = h;
+    }
+    split3(n2, v[21], v[22], v[23]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) op[c][e] = v[8 * c + e];
+}
+
+// One set of 32 queries of a wave, one per column; lanes l and l + 32 share a
+// query (each sees 16 of a tile's 32 nodes).
+template <int MODE>
+struct FilterQueries {
+    bf16x8 b0, b1;          // operand columns: places 8 (l / 32) .. + 7, and 16 more
+    float x[kMaxDof], aq, q2;
+    float best, thr;        // the lane's own best key; the least key known for the query
+    int32_t bi, q;
+    bool act;
+
+    // places 24 .. 26 (lanes 32 ..): the constant for the present bound
+    __device__ __forceinline__ void set_bound(float wide, float &h) {
+        float c;
+        if (MODE == kScanConfig) {
+            // no bound yet: everything passes
+            c = thr < INFINITY ? q2 - (thr * (1.0f + kFilterSlack) + 1e-30f) : kFilterPass;
+            h = 0.f;
+        } else {
+            // no bound yet: the cone alone (w2 <= wide for every node of the round)
+            h = thr < INFINITY ? 0.5f * thr : wide;
+            c = q2 - (h + (h * kFilterSlack + 1e-30f));
+        }
+        if (!(q2 < kFilterMax) || !(h < kFilterMax)) c = kFilterPass, h = 0.f;
+        if (!act) c = kFilterMax;
+        if (threadIdx.x & 32) {
+            __bf16 u, v, w;
+            split3(c, u, v, w);
+            b1[0] = u;
+            b1[1] = v;
+            b1[2] = w;
+        }
+    }
+    __device__ __forceinline__ void load(const ScanArgs &a, float sv, int d, bool act_, int32_t q_) {
+        act = act_;
+        q = q_;
+        q2 = 0.f;
+#pragma unroll
+        for (int j = 0; j < kMaxDof; ++j) {
+            x[j] = (act && j < d) ? a.qx[(int64_t)q * a.sq + (int64_t)j * a.sj] : 0.f;
+            q2 = fmaf(x[j], x[j], q2);
+        }
+        aq = act ? sv * a.qt[(int64_t)q * a.st] : 0.f;
+        best = thr = INFINITY;
+        bi = -1;
+        const bool plain = q2 < kFilterMax;
+        q2 *= 1.0f - kFilterEps;
+        __bf16 v[32];
+#pragma unroll
+        for (int j = 0; j < kMaxDof; ++j) {
+            const float c = plain ? x[j] : 0.f;
+            const __bf16 h = (__bf16)c;
+            v[3 * j] = v[3 * j + 1] = (__bf16)(-2.f * (float)h);
+            v[3 * j + 2] = (__bf16)(-2.f * (float)(__bf16)(c - (float)h));
+        }
+        v[21] = v[22] = v[23] = (__bf16)1.f;
+#pragma unroll
+        for (int e = 24; e < 32; ++e) v[e] = (__bf16)0.f;
+        bf16x8 w[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) w[k][e] = v[8 * k + e];
+        const bool up = threadIdx.x & 32;
+        b0 = w[0];
+        b1 = w[2];
+        if (up) b0 = w[1];
+        if (up) b1 = w[3];
+    }
+    // the plain scan's test of one staged node
+    __device__ __forceinline__ void test(const float4 &lo, const float4 &hi, int32_t idx) {
+        const float xs[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+        float D2 = 0.f;
+#pragma unroll
+        for (int j = 0; j < kMaxDof; ++j) {
+            const float e = xs[j] - x[j];
+            D2 = fmaf(e, e, D2);
+        }
+        float key = D2;
+        bool ok = act;
+        if (MODE == kScanRho) {
+            const float vd = aq - xs[7];
+            const float w2 = vd * fabsf(vd);
+            ok = ok && (D2 <= w2) && (w2 > 0.f);
+            key = fmaf(vd, fabsf(vd), D2);
+        }
+        if (ok && (key < best || (key == best && idx < bi))) {
+            best = key;
+            bi = idx;
+        }
+    }
+    // the query's two lanes agree on the better of their bests
+    __device__ __forceinline__ void pair() {
+        const float ob = __shfl_xor(best, 32, 64);
+        const int32_t oi = __shfl_xor(bi, 32, 64);
+        if (ob < best || (ob == best && (uint32_t)oi < (uint32_t)bi)) {
+            best = ob;
+            bi = oi;
+        }
+        thr = fminf(thr, best);
+    }
+    // the other slices' bests, and this one's for them
+    __device__ __forceinline__ void share(unsigned long long *keys) {
+        unsigned long long k = kNoKey;
+        if (act && !(threadIdx.x & 32)) {
+            const unsigned long long own = bi >= 0 ? pack_key(best, bi) : kNoKey;
+            k = own != kNoKey ? atomicMin(&keys[q], own)
+                              : __hip_atomic_load(&keys[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        thr = fminf(thr, k == kNoKey ? INFINITY : __uint_as_float((uint32_t)(k >> 32)));
+        thr = fminf(thr, __shfl_xor(thr, 32, 64));
+    }
+    __device__ __forceinline__ void finish(unsigned long long *keys) const {
+        if (act && bi >= 0 && best <= thr && !(threadIdx.x & 32)) atomicMin(&keys[q], pack_key(best, bi));
+    }
+};
+
 // One block = one tile of up to TQ queries (one per thread) against the
 // y-th of nch slices of its node set.  The set is a single pool or the
 // concatenation of the backward pools; nodes stream through LDS in rounds of
@@ -375,6 +574,9 @@ __global__ __launch_bounds__(TQ) void k_scan(ScanArgs a0, const ScanArgs *__rest
     __shared__ __align__(16) float sx[TQ][8];
     __shared__ float sT[TQ];
     __shared__ int32_t sI[TQ];
+    constexpr bool kFilter = MODE != kScanBridge && TQ == kTileQ;
+    __shared__ bf16x8 s_op[kFilter ? 3 : 1][kFilter ? TQ : 1];  // the filter's operand rows, eight places apart
+    __shared__ int s_wide[4];
     __shared__ int32_t s_pool[kMaxPools + 1], s_pre[kMaxPools + 1], s_cnt[kMaxPools + 1];
     __shared__ int32_t s_np;
     const ScanArgs &a = MULTI ? av[members[blockIdx.z]] : a0;
@@ -455,27 +657,17 @@ __global__ __launch_bounds__(TQ) void k_scan(ScanArgs a0, const ScanArgs *__rest
     // merge into start empty).  Bridge scans keep every slice: their merge
     // reads one partial result per slice.
     int nch = a.nch;
+    // (the same for the whole block)
+    const int set_q = kFilter ? (a.bmode == 0 ? TQ * a.n_tiles[0] : a.bcnt[set]) : 0;
+    const bool filter = kFilter && n >= kFilterMinQueries && set_q * total >= kFilterMinPairs;
     if (MODE != kScanBridge) {
-        const int64_t want = (total + kMinSliceNodes - 1) / kMinSliceNodes;
+        const int slice = filter ? kFilterSlice : kMinSliceNodes;
+        int64_t want = (total + slice - 1) / slice;
+        if (filter) want = min<int64_t>(want, max(kFilterBlocks / ((set_q + TQ - 1) / TQ), 1));
         nch = (int)min<int64_t>(nch, max<int64_t>(want, 1));
         if ((int)blockIdx.y >= nch) return;
     }
-    // lanes per query: as many as the tile's queries leave free (a power of
-    // two, at most a wave); lane `sub` of a query takes every L-th node of a
-    // round, and the query's L lanes combine their bests at the end
-    int lq_shift = 0;
-    while (lq_shift < 6 && n * (2 << lq_shift) <= TQ) ++lq_shift;
-    const int L = 1 << lq_shift, qs = tid >> lq_shift, sub = tid & (L - 1);
-    const bool act = qs < n;
-    const int q = act ? (qrow >= 0 ? a.border[qrow + tile.y + qs] : tile.y + qs) : 0;
     const int64_t c0 = (int64_t)blockIdx.y * total / nch, c1 = (int64_t)(blockIdx.y + 1) * total / nch;
-    float qx[kMaxDof];
-    float aq = 0.f;
-#pragma unroll
-    for (int j = 0; j < kMaxDof; ++j) qx[j] = (act && j < d) ? a.qx[(int64_t)q * a.sq + (int64_t)j * a.sj] : 0.f;
-    if (act) aq = sv * a.qt[(int64_t)q * a.st];
-    float best = INFINITY, bestT = INFINITY;
-    int32_t bi = -1;
     const float *X = a.tree.x;
     const int64_t total_cap = a.tree.total;
     const float nanf_ = __int_as_float(0x7fc00000);
@@ -503,6 +695,139 @@ __global__ __launch_bounds__(TQ) void k_scan(ScanArgs a0, const ScanArgs *__rest
             rI = (int32_t)gi;
         }
     };
+    if constexpr (kFilter) {
+        if (filter) {
+            // 64 queries per wave; waves that the queries leave free share the nodes
+            const int lane = tid & 63, wv = tid >> 6;
+            const int qw = (n + 63) / 64, parts = 4 / qw, part = wv / qw;
+            const bool on = part < parts;
+            const int q0 = (wv % qw) * 64 + (lane & 31);
+            FilterQueries<MODE> Q[2];
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                const int qi = q0 + 32 * f;
+                const bool act = on && qi < n;
+                Q[f].load(a, sv, d, act, act ? (qrow >= 0 ? a.border[qrow + tile.y + qi] : tile.y + qi) : 0);
+            }
+            const float4 *sx4 = reinterpret_cast<const float4 *>(&sx[0][0]);
+            bf16x8 ones;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ones[e] = (__bf16)(e < 3 ? 1.f : 0.f);
+            if (c0 < c1) fetch(c0);
+            for (int64_t c = c0; c < c1; c += TQ) {
+                __syncthreads();
+                const bool used = c + tid < c1;
+                {
+                    bf16x8 op[3];
+                    filter_node(rx, used, op);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) s_op[k][tid] = op[k];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) sx[tid][j] = rx[j];
+                    sT[tid] = rx[7];
+                    sI[tid] = rI;
+                    if (MODE == kScanRho) {
+                        // the round's largest |sigma v t| (finite ones)
+                        int w = __float_as_int(fabsf(rx[7]));
+                        w = used && w < 0x7f800000 ? w : 0;
+                        w = wave_scan(w, 0, [](int x, int y) { return max(x, y); });
+                        if (lane == 63) s_wide[wv] = w;
+                    }
+                }
+                __syncthreads();
+                if (c + TQ < c1) fetch(c + TQ);
+                const int m = (int)min<int64_t>(TQ, c1 - c);
+                if (!on) continue;
+                int k0 = 0;
+                if (c == c0) {
+                    // the slice's first nodes exactly, the query's two lanes and the parts in turn
+                    k0 = min(m, kFilterSeed);
+                    for (int k = 2 * part + (lane >> 5); k < k0; k += 2 * parts) {
+                        const float4 lo = sx4[2 * k], hi = sx4[2 * k + 1];
+                        const int32_t idx = sI[k];
+                        Q[0].test(lo, hi, idx);
+                        Q[1].test(lo, hi, idx);
+                    }
+                }
+                float h[2];
+                const int round = (int)((c - c0) / TQ);
+                const float tw = MODE == kScanRho ? __int_as_float(max(max(s_wide[0], s_wide[1]), max(s_wide[2], s_wide[3]))) : 0.f;
+#pragma unroll
+                for (int f = 0; f < 2; ++f) {
+                    if (c == c0) Q[f].pair();
+                    if (round == 0 || round == 1 || round == 4) Q[f].share(a.keys);
+                    const float w = fabsf(Q[f].aq) + tw;
+                    Q[f].set_bound(w * w, h[f]);
+                }
+                for (int k = k0 + 32 * part; k < m; k += 32 * parts) {
+                    const int row = k + (lane & 31);  // (k0 and 32 divide 256: a tile stays in the round)
+                    const bf16x8 a0 = s_op[lane >> 5][row];
+                    bf16x8 a1 = s_op[2][row];
+                    if (lane & 32) a1 = ones;
+                    float tt[16];
+                    const int r0 = k + 4 * (lane >> 5);  // the lane's rows: r0 + 8 (r / 4) + r % 4
+                    if (MODE == kScanRho) {
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            const float4 u = *reinterpret_cast<const float4 *>(&sT[r0 + 8 * g]);
+                            tt[4 * g] = u.x;
+                            tt[4 * g + 1] = u.y;
+                            tt[4 * g + 2] = u.z;
+                            tt[4 * g + 3] = u.w;
+                        }
+                    }
+#pragma unroll
+                    for (int f = 0; f < 2; ++f) {
+                        f32x16 acc = {};
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, Q[f].b0, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, Q[f].b1, acc, 0, 0, 0);
+                        float least = INFINITY;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            if (MODE == kScanRho) {
+                                const float vd = Q[f].aq - tt[r];
+                                acc[r] += fabsf(fmaf(vd, fabsf(vd), -h[f]));
+                            }
+                            least = fminf(least, acc[r]);
+                        }
+                        if (__ballot(least <= 0.f) == 0) continue;
+                        unsigned mask = 0;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) mask |= acc[r] <= 0.f ? 1u << r : 0u;
+                        while (__ballot(mask != 0) != 0) {
+                            const int r = mask ? __builtin_ctz(mask) : 0;
+                            const int w = r0 + 8 * (r >> 2) + (r & 3);
+                            if (mask && w < m) Q[f].test(sx4[2 * w], sx4[2 * w + 1], sI[w]);
+                            mask &= mask - 1;
+                        }
+                        Q[f].pair();
+                        const float w = fabsf(Q[f].aq) + tw;
+                        Q[f].set_bound(w * w, h[f]);
+                    }
+                }
+            }
+            if (on) {
+                Q[0].finish(a.keys);
+                Q[1].finish(a.keys);
+            }
+            return;
+        }
+    }
+    // lanes per query: as many as the tile's queries leave free (a power of
+    // two, at most a wave); lane `sub` of a query takes every L-th node of a
+    // round, and the query's L lanes combine their bests at the end
+    int lq_shift = 0;
+    while (lq_shift < 6 && n * (2 << lq_shift) <= TQ) ++lq_shift;
+    const int L = 1 << lq_shift, qs = tid >> lq_shift, sub = tid & (L - 1);
+    const bool act = qs < n;
+    const int q = act ? (qrow >= 0 ? a.border[qrow + tile.y + qs] : tile.y + qs) : 0;
+    float qx[kMaxDof];
+    float aq = 0.f;
+#pragma unroll
+    for (int j = 0; j < kMaxDof; ++j) qx[j] = (act && j < d) ? a.qx[(int64_t)q * a.sq + (int64_t)j * a.sj] : 0.f;
+    if (act) aq = sv * a.qt[(int64_t)q * a.st];
+    float best = INFINITY, bestT = INFINITY;
+    int32_t bi = -1;
     if (c0 < c1) fetch(c0);
     for (int64_t c = c0; c < c1; c += TQ) {
         __syncthreads();
@@ -538,7 +863,8 @@ __global__ __launch_bounds__(TQ) void k_scan(ScanArgs a0, const ScanArgs *__rest
                     const float vd = aq - xs[7];
                     const float w2 = vd * fabsf(vd);
                     const bool adm = (D2 <= w2) && (w2 > 0.f);
-                    const float key = D2 + w2;
+                    // (roundings fixed by hand: every scan of a metric has to agree bit for bit)
+                    const float key = MODE == kScanRho ? fmaf(vd, fabsf(vd), D2) : __fadd_rn(D2, w2);
                     if (MODE == kScanRho) {
                         if (adm && key < best) { best = key; kb = k; }
                     } else {
