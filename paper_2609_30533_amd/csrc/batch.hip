@@ -455,11 +455,7 @@ int st_path_get(st_problem *p, st_path *out) {
     out->arrival = INFINITY;
     out->length = INFINITY;
     ST_HIP(hipDeviceSynchronize());
-    hipStream_t s = nullptr;
-    ST_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
-    const int rc = fetch_path(p, s, out);
-    (void)hipStreamDestroy(s);
-    return rc;
+    return fetch_path(p, nullptr, out);
 }
 
 }  // extern "C"

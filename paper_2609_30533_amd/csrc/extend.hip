@@ -1710,23 +1710,64 @@ __global__ void k_fill_tiles(int64_t M, int set, int sigma, int4 *tiles, int32_t
 // path extraction and timestamps
 // ---------------------------------------------------------------------------
 
-// Lengths of the incumbent's forward chain (v_f back to the root) and
-// backward chain (w_b to its root).  A chain only points to earlier nodes of
-// its own pool, so it cannot be longer than that pool's node count; a longer
-// walk means a corrupted tree and is reported as -1.
-__global__ void k_path_len(TreeDev tree, const PlanDev *pl, int32_t *len_out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const int32_t f = pl->inc_f, b = pl->inc_b;
-    len_out[0] = len_out[1] = 0;
-    if (f < 0 || b < 0) return;
-    const int32_t heads[2] = {f, b};
-    for (int c = 0; c < 2; ++c) {
-        const int64_t limit = tree.total;
-        int64_t n = 0;
-        for (int32_t i = heads[c]; i >= 0 && n <= limit; i = tree.parent[i]) ++n;
-        len_out[c] = n > limit ? -1 : (int32_t)n;
+// The incumbent and its path into pinned host memory, one wave: the chain
+// lengths (forward from v_f back to the root, backward from w_b to its root) by
+// one lane, then, when the path fits, its states by all lanes, the forward chain
+// root first.  A chain only points to earlier nodes of its own pool, so it
+// cannot be longer than the trees; a longer walk means a corrupted tree and is
+// reported as -1.
+__global__ __launch_bounds__(64) void k_path_view(TreeDev tree, const PlanDev *pl, HostView *v) {
+    __shared__ int32_t s_idx[kViewStates], s_len[2];
+    const int lane = threadIdx.x, d = tree.d, W = d + 1;
+    if (lane == 0) {
+        const int32_t f = pl->inc_f, b = pl->inc_b;
+        const bool none = f < 0 || b < 0;
+        int total = 0;
+        for (int c = 0; c < 2; ++c) {
+            int64_t n = 0;
+            for (int32_t i = none ? -1 : (c == 0 ? f : b); i >= 0 && n <= tree.total; i = tree.parent[i]) {
+                if (total < kViewStates) s_idx[total] = i;
+                ++total;
+                ++n;
+            }
+            s_len[c] = n > tree.total ? -1 : (int32_t)n;
+            if (s_len[c] < 0) break;
+        }
+        v->nf = s_len[0];
+        v->nb = s_len[0] < 0 ? 0 : s_len[1];
+        v->U = pl->U;
+        v->C = pl->C;
+        v->first_iter = pl->first_iter;
+        v->overflow = pl->overflow;
+    }
+    __syncthreads();
+    const int nf = s_len[0], n = nf < 0 || s_len[1] < 0 ? 0 : nf + s_len[1];
+    if (n > kViewStates) return;
+    for (int k = lane; k < n * W; k += 64) {
+        const int j = k / W, c = k - j * W;
+        v->states[k] = tree.x[(int64_t)c * tree.total + s_idx[j < nf ? nf - 1 - j : j]];
     }
 }
+
+// The fresh state of a problem (one block): the planner state, the forward root
+// (q_s, 0) and, with recycling, every active slot's root (q_g, T).
+__global__ __launch_bounds__(256) void k_init_state(SceneDev sc, TreeDev tree, PlanDev *pl, const PlanDev *fresh,
+                                                    int32_t variant) {
+    const int32_t *src = reinterpret_cast<const int32_t *>(fresh);
+    for (int i = threadIdx.x; i < (int)(sizeof(PlanDev) / 4); i += blockDim.x) reinterpret_cast<int32_t *>(pl)[i] = src[i];
+    const int n = variant == ST_ROOT_RECYCLING ? tree.n_pools : 1;
+    for (int p = threadIdx.x; p < n; p += blockDim.x) {
+        if (p > 0 && !fresh->slot_active[p - 1]) continue;
+        const float T = p > 0 ? fresh->slotT[p - 1] : 0.f;
+        const int64_t i = pool_base(tree, p);
+        for (int j = 0; j < tree.d; ++j) tree.x[(int64_t)j * tree.total + i] = p > 0 ? sc.q_g[j] : sc.q_s[j];
+        tree.x[(int64_t)tree.d * tree.total + i] = T;
+        tree.parent[i] = -1;
+        tree.cost[i] = 0.f;
+        tree.rootT[i] = T;
+    }
+}
+static_assert(sizeof(PlanDev) % 4 == 0, "copied word by word");
 
 // The incumbent path into out[(nf + nb)][d+1]: the forward chain written back
 // to front (root first), then the backward chain from w_b to its root.
@@ -2316,98 +2357,118 @@ static int iterate(st_problem *p, int64_t iters, hipStream_t s) {
     return ST_OK;
 }
 
+hipError_t launch_init_state(st_problem *p) {
+    k_init_state<<<1, 256>>>(p->sc, p->tree, p->d_plan, p->d_plan0, p->prm.variant);
+    return hipGetLastError();
+}
+
+// What the planning calls keep in the handle instead of making and releasing it
+// on every call: pinned memory that the kernels write their few results into
+// and, for st_plan, a stream and the two events of its clock (a batch's members
+// need neither, and a batch may have 4096).  The caller holds view_mu.
+static int view_prepare(st_problem *p) {
+    if (!p->view) ST_HIP(hipHostMalloc((void **)&p->view, sizeof(HostView), hipHostMallocDefault));
+    return ST_OK;
+}
+
+static int plan_prepare(st_problem *p) {
+    std::lock_guard<std::mutex> lock(p->view_mu);
+    if (!p->plan_stream) ST_HIP(hipStreamCreateWithFlags(&p->plan_stream, hipStreamNonBlocking));
+    for (hipEvent_t &e : p->plan_ev)
+        if (!e) ST_HIP(hipEventCreate(&e));
+    return view_prepare(p);
+}
+
+void view_free(st_problem *p) {
+    if (p->plan_stream) (void)hipStreamDestroy(p->plan_stream);
+    p->plan_stream = nullptr;
+    if (p->view) (void)hipHostFree(p->view);
+    p->view = nullptr;
+    for (hipEvent_t &e : p->plan_ev) {
+        if (e) (void)hipEventDestroy(e);
+        e = nullptr;
+    }
+}
+
 // Start state check and the trivial case q_s = q_g (arrival at time 0 when
 // the arrival range allows it).  Synchronous.
 int start_check(st_problem *p, bool *start_free, bool *trivial) {
-    const int d = p->d, W = d + 1;
+    std::lock_guard<std::mutex> lock(p->view_mu);
+    const int rc = view_prepare(p);
+    if (rc != ST_OK) return rc;
     bool same = true;
-    for (int j = 0; j < d; ++j) same = same && p->q_s[j] == p->q_g[j];
-    float *dx = nullptr;
-    uint8_t *dfree = nullptr;
-    ST_HIP(hipMalloc((void **)&dx, W * sizeof(float)));
-    ST_HIP(hipMalloc((void **)&dfree, 1));
-    std::vector<float> xs(W);
-    for (int j = 0; j < d; ++j) xs[j] = (float)p->q_s[j];
-    xs[d] = 0.f;
-    ST_HIP(hipMemcpy(dx, xs.data(), W * sizeof(float), hipMemcpyHostToDevice));
-    ST_HIP(launch_check_states(p->sc, 1, dx, dfree, 0));
-    uint8_t f = 0;
-    ST_HIP(hipMemcpy(&f, dfree, 1, hipMemcpyDeviceToHost));
-    (void)hipFree(dx);
-    (void)hipFree(dfree);
-    *start_free = f != 0;
+    for (int j = 0; j < p->d; ++j) same = same && p->q_s[j] == p->q_g[j];
+    p->view->start_free = 0;
+    ST_HIP(launch_check_states(p->sc, 1, p->d_start, reinterpret_cast<uint8_t *>(&p->view->start_free),
+                               nullptr));
+    ST_HIP(hipStreamSynchronize(nullptr));
+    const bool f = p->view->start_free != 0;
+    *start_free = f;
     *trivial = same && f && p->L <= 0.0;
     return ST_OK;
 }
 
 // The incumbent path (forward chain, then backward chain) into host memory.
-// The chain lengths are read first, so the copy is sized exactly.
 int fetch_path(st_problem *p, hipStream_t s, st_path *out) {
+    std::lock_guard<std::mutex> lock(p->view_mu);
+    const int rc = view_prepare(p);
+    if (rc != ST_OK) return rc;
     const int W = p->d + 1;
-    int32_t *dlen = nullptr;
-    float *dpath = nullptr;
-    PlanDev host;
-    int32_t len[2] = {0, 0};
-    int rc = ST_OK;
-    if (hipMalloc((void **)&dlen, 2 * sizeof(int32_t)) != hipSuccess) {
-        set_error("path extraction: out of device memory");
-        return ST_ENOMEM;
-    }
-    k_path_len<<<1, 1, 0, s>>>(p->tree, p->d_plan, dlen);
-    if (hipGetLastError() != hipSuccess ||
-        hipMemcpyAsync(len, dlen, sizeof len, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(&host, p->d_plan, sizeof(PlanDev), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) {
+    HostView *v = p->view;
+    k_path_view<<<1, 64, 0, s>>>(p->tree, p->d_plan, v);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
         set_error("path extraction: device copy failed");
-        rc = ST_EHIP;
-    } else if (len[0] < 0 || len[1] < 0) {
+        return ST_EHIP;
+    }
+    if (v->nf < 0 || v->nb < 0) {
         set_error("path extraction: a parent chain does not end at a root");
-        rc = ST_EHIP;
+        return ST_EHIP;
     }
-    const int64_t n = (int64_t)len[0] + len[1];
-    if (rc == ST_OK && n > 0) {
-        if (hipMalloc((void **)&dpath, (size_t)n * W * sizeof(float)) != hipSuccess) {
-            set_error("path extraction: out of device memory");
-            rc = ST_ENOMEM;
-        } else {
-            std::vector<float> buf((size_t)n * W);
-            k_path_copy<<<1, 1, 0, s>>>(p->tree, p->d_plan, len[0], len[1], dpath);
-            if (hipGetLastError() != hipSuccess ||
-                hipMemcpyAsync(buf.data(), dpath, buf.size() * sizeof(float), hipMemcpyDeviceToHost, s) != hipSuccess ||
-                hipStreamSynchronize(s) != hipSuccess) {
+    const int64_t n = (int64_t)v->nf + v->nb;
+    if (n > 0) {
+        std::vector<float> buf;
+        const float *states = v->states;
+        if (n > kViewStates) {
+            float *dpath = nullptr;
+            if (hipMalloc((void **)&dpath, (size_t)n * W * sizeof(float)) != hipSuccess) {
+                set_error("path extraction: out of device memory");
+                return ST_ENOMEM;
+            }
+            buf.resize((size_t)n * W);
+            k_path_copy<<<1, 1, 0, s>>>(p->tree, p->d_plan, v->nf, v->nb, dpath);
+            const bool bad = hipGetLastError() != hipSuccess ||
+                             hipMemcpyAsync(buf.data(), dpath, buf.size() * sizeof(float), hipMemcpyDeviceToHost, s) !=
+                                 hipSuccess ||
+                             hipStreamSynchronize(s) != hipSuccess;
+            (void)hipFree(dpath);
+            if (bad) {
                 set_error("path extraction: device copy failed");
-                rc = ST_EHIP;
-            } else {
-                out->n_states = n;
-                out->states = (double *)malloc(sizeof(double) * buf.size());
-                if (!out->states) {
-                    set_error("path extraction: out of host memory");
-                    rc = ST_ENOMEM;
-                    out->n_states = 0;
-                } else {
-                    for (size_t i = 0; i < buf.size(); ++i) out->states[i] = buf[i];
-                }
+                return ST_EHIP;
             }
+            states = buf.data();
         }
-    }
-    if (rc == ST_OK) {
-        out->dof = p->d;
-        out->iterations = p->iter;
-        out->arrival = host.U;
-        out->length = host.C;
-        if (host.first_iter >= 0) out->first_solution_iter = host.first_iter;
-        if (n == 0) {
-            rc = ST_NO_SOLUTION;
-            // growth stopped by full pools is reported as a capacity error
-            if (host.overflow) {
-                set_error("no solution and the tree capacity is exhausted (inserts were dropped)");
-                rc = ST_ECAPACITY;
-            }
+        out->states = (double *)malloc(sizeof(double) * (size_t)n * W);
+        if (!out->states) {
+            set_error("path extraction: out of host memory");
+            return ST_ENOMEM;
         }
+        out->n_states = n;
+        for (int64_t i = 0; i < n * W; ++i) out->states[i] = states[i];
     }
-    if (dpath) (void)hipFree(dpath);
-    (void)hipFree(dlen);
-    return rc;
+    out->dof = p->d;
+    out->iterations = p->iter;
+    out->arrival = v->U;
+    out->length = v->C;
+    if (v->first_iter >= 0) out->first_solution_iter = v->first_iter;
+    if (n == 0) {
+        // growth stopped by full pools is reported as a capacity error
+        if (v->overflow) {
+            set_error("no solution and the tree capacity is exhausted (inserts were dropped)");
+            return ST_ECAPACITY;
+        }
+        return ST_NO_SOLUTION;
+    }
+    return ST_OK;
 }
 
 }  // namespace st
@@ -2509,17 +2570,16 @@ int st_plan(st_problem *p, const st_budget *b, st_path *out) {
     }
     // work the caller queued on other streams (state import, proposal) comes first
     ST_HIP(hipDeviceSynchronize());
-    hipStream_t s = nullptr;
-    ST_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
-    PlanDev *host = nullptr;
-    ST_HIP(hipHostMalloc((void **)&host, sizeof(PlanDev), hipHostMallocDefault));
+    int rc = plan_prepare(p);
+    if (rc != ST_OK) return rc;
+    hipStream_t s = p->plan_stream;
+    PlanDev *host = &p->view->plan;
     // the launch set-up (buffers, graph capture) before the first solution's
     // clock, which then runs on the device: from an event ahead of the first
     // launch to one behind the launches that found the solution
-    int rc = iterate_prepare(p);
-    hipEvent_t ev[2] = {nullptr, nullptr};
-    if (rc == ST_OK && (hipEventCreate(&ev[0]) != hipSuccess || hipEventCreate(&ev[1]) != hipSuccess ||
-                        hipEventRecord(ev[0], s) != hipSuccess)) {
+    rc = iterate_prepare(p);
+    hipEvent_t *ev = p->plan_ev;
+    if (rc == ST_OK && hipEventRecord(ev[0], s) != hipSuccess) {
         set_error("st_plan: event set-up failed");
         rc = ST_EHIP;
     }
@@ -2554,10 +2614,6 @@ int st_plan(st_problem *p, const st_budget *b, st_path *out) {
         if (b->max_iters <= 0 && b->max_ms <= 0 && !b->stop_at_first) break;
     }
     if (rc == ST_OK) rc = fetch_path(p, s, out);
-    for (hipEvent_t e : ev)
-        if (e) (void)hipEventDestroy(e);
-    (void)hipHostFree(host);
-    (void)hipStreamDestroy(s);
     out->total_ms = ms_since();
     return rc;
 }

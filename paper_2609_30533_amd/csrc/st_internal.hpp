@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <string>
+#include <mutex>
 #include <vector>
 
 #include "../../include/st.h"
@@ -159,6 +160,19 @@ struct Work {
     float *Up, *Cp;
 };
 
+// Results that kernels write straight into pinned host memory, read after one
+// synchronisation: the start check, the incumbent and its path (a longer path
+// is fetched through a buffer of its own size).
+constexpr int kViewStates = 128;
+struct HostView {
+    PlanDev plan;
+    int32_t start_free;
+    int32_t nf, nb;            // chain lengths, -1 for a chain without an end
+    float U, C;
+    int32_t first_iter, overflow;
+    float states[kViewStates * 8];  // [nf + nb][d + 1], when they fit
+};
+
 }  // namespace st
 
 struct st_problem {
@@ -198,6 +212,16 @@ struct st_problem {
     hipGraphExec_t graph[2] = {nullptr, nullptr};
     int64_t graph_B = 0;
     hipStream_t cap_stream = nullptr;
+    // a fresh problem's planner state and the start state, uploaded at creation
+    st::PlanDev *d_plan0 = nullptr;
+    float *d_start = nullptr;
+    // what the planning calls keep (made by the first such call): pinned results,
+    // a stream and the events of its clock.  The mutex covers the making and one
+    // use of the results, so threads may read one handle's path together.
+    std::mutex view_mu;
+    hipStream_t plan_stream = nullptr;
+    hipEvent_t plan_ev[2] = {nullptr, nullptr};
+    st::HostView *view = nullptr;
     // optional stage timing with HIP events (stage id per recorded event)
     bool prof = false;
     std::vector<hipEvent_t> prof_ev;
@@ -271,6 +295,9 @@ void work_free(st_problem *p);
 void graphs_free(st_problem *p);
 
 // ---- allocation ------------------------------------------------------------
-hipError_t launch_roots_update(st_problem *p, hipStream_t s);
+// The fresh planner state and its roots, from d_plan0 (async on the null stream).
+hipError_t launch_init_state(st_problem *p);
+// Releases the planning calls' pinned results, stream and events.
+void view_free(st_problem *p);
 
 }  // namespace st
