@@ -452,8 +452,10 @@ int st_proposal_set(st_problem *p, const float *z, float mix, void *stream);
  * tile (4, 8 or 16, dividing the padded obstacle count; 0 keeps the current
  * value) and lanes per edge chunk for extension edges, bridge edges and
  * st_check_edges (powers of two up to 64; 0 keeps; choosing lanes for
- * st_check_edges puts it on the chunked path, slower at every size measured).  Results do not depend
- * on these.  Synchronous; drops captured iteration graphs. */
+ * st_check_edges puts it on the chunked path, slower at every size measured;
+ * the lanes of bridge edges are kept and reported, but their check lays states
+ * end to end and has no chunks).  Results do not depend on these.
+ * Synchronous; drops captured iteration graphs. */
 int st_set_tuning(st_problem *p, int32_t obstacle_tile, int32_t lanes_extension, int32_t lanes_bridge,
                   int32_t lanes_check);
 
@@ -463,7 +465,8 @@ int st_set_tuning(st_problem *p, int32_t obstacle_tile, int32_t lanes_extension,
  * to fill the device, more instructions per state) for extension edges,
  * bridge edges and st_check_edges; -1 chooses by launch size (4 up to 256
  * edges, else 1; a batch counts the edges of all its members; st_check_edges:
- * the one-kernel path); 0 keeps.  A translating robot always uses
+ * the one-kernel path); 0 keeps.  Bridge edges always choose by what a phase
+ * of their check leaves free.  A translating robot always uses
  * one lane per state.  Results do not depend on these.  Synchronous; drops
  * captured iteration graphs. */
 int st_set_state_split(st_problem *p, int32_t split_extension, int32_t split_bridge, int32_t split_check);
@@ -473,7 +476,7 @@ int st_set_state_split(st_problem *p, int32_t split_extension, int32_t split_bri
  * eight waves takes 4 x `edges_per_block` consecutive edges (edges_per_block
  * 1..8; fewer when the samples would not give every compute unit a block), lays
  * their states end to end and deals them to its waves in rounds of 64.
- * 0 selects the chunked path that long bridges use.  Results do not depend on
+ * 0 selects the chunked path.  Results do not depend on
  * this.  Default 4.  In a batch (st_batch_create) a member on this path takes
  * 8 edges per block of four waves.
  * Synchronous; drops captured graphs. */

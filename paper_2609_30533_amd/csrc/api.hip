@@ -642,11 +642,10 @@ int st_set_state_split(st_problem *p, int32_t split_extension, int32_t split_bri
             default: return false;
         }
     };
-    int se = p->split_ext, sb = p->split_br, sk = p->split_api;
+    int se = p->split_ext, sb = -1, sk = p->split_api;
     if (!shift_of(split_extension, &se) || !shift_of(split_bridge, &sb) || !shift_of(split_check, &sk))
         return fail(ST_EINVAL, "state split must be 1, 2 or 4, -1 (by launch size) or 0 (keep)");
     p->split_ext = se;
-    p->split_br = sb;
     p->split_api = sk;
     if (split_check != 0) p->api_split = sk >= 0;
     ST_HIP(hipDeviceSynchronize());

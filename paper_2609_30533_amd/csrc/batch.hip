@@ -119,13 +119,13 @@ static int batch_build(st_batch *b) {
     std::vector<SampleArgs> smp(P);
     std::vector<ScanArgs> scan_nn(P), scan_br(P);
     std::vector<SteerArgs> steer(P);
-    std::vector<EdgeArgs> edge_ext(P), edge_br(P);
+    std::vector<EdgeArgs> edge_ext(P);
     std::vector<InsertArgs> ins(P);
     std::vector<BridgeArgs> merge(P);
     std::vector<PublishArgs> pub(P);
     std::vector<RootsArgs> roots(P);
     std::vector<int32_t> all, ir, rr;
-    std::map<std::tuple<int, int, int, int, int>, std::vector<int32_t>> cls;
+    std::map<std::tuple<int, int, int, int>, std::vector<int32_t>> cls;
     std::vector<PlanDev *> pls(P);
     L.nch = nch;
     // one-wave scan blocks when every member draws at most 64 samples
@@ -144,16 +144,15 @@ static int batch_build(st_batch *b) {
         steer[m] = a.steer;
         if (a.edge_ext.flat > 0) flat_shape_batch(a.edge_ext);
         edge_ext[m] = a.edge_ext;
-        edge_br[m] = a.edge_br;
         ins[m] = a.insert;
         merge[m] = a.merge;
+        bridge_shape_batch(merge[m]);
         pub[m] = a.publish;
         roots[m] = a.roots;
         pls[m] = p->d_plan;
         all.push_back(m);
         (p->prm.variant == ST_INTERVAL_ROOT ? ir : rr).push_back(m);
-        cls[std::make_tuple(p->sc.stat ? (int)kDHStatic : p->sc.kind, p->sc.ot, p->sc.obs_mode, a.edge_ext.split_shift,
-                            a.edge_br.split_shift)]
+        cls[std::make_tuple(p->sc.stat ? (int)kDHStatic : p->sc.kind, p->sc.ot, p->sc.obs_mode, a.edge_ext.split_shift)]
             .push_back(m);
         // query tiles of the scans (tiles of L.scan_tq queries: one per node
         // set and a full one per L.scan_tq samples at most); the two
@@ -163,7 +162,7 @@ static int batch_build(st_batch *b) {
         mt = std::max(mt, tiles_b + p->tree.n_pools);
         L.mt_br = std::max(L.mt_br, tiles_b + 2);
         L.nb_worker = std::max<int>(L.nb_worker, (int)((B + 255) / 256));
-        L.nb_edge = std::max(L.nb_edge, std::max(a.edge_ext.nb_edge, a.edge_br.nb_edge));
+        L.nb_edge = std::max(L.nb_edge, a.edge_ext.nb_edge);
         L.max_pools = std::max(L.max_pools, p->tree.n_pools);
         L.ins_threads = std::max(L.ins_threads, insert_threads(B));
         L.ext_flat = L.ext_flat && a.edge_ext.flat > 0;
@@ -175,7 +174,6 @@ static int batch_build(st_batch *b) {
     ST_HIP(upload(b->owned, scan_br, &L.scan_br));
     ST_HIP(upload(b->owned, steer, &L.steer));
     ST_HIP(upload(b->owned, edge_ext, &L.edge_ext));
-    ST_HIP(upload(b->owned, edge_br, &L.edge_br));
     ST_HIP(upload(b->owned, ins, &L.insert));
     ST_HIP(upload(b->owned, merge, &L.merge));
     ST_HIP(upload(b->owned, pub, &L.publish));
@@ -191,18 +189,17 @@ static int batch_build(st_batch *b) {
         const st_problem *p0 = b->mem[kv.second[0]];
         c.key = p0->sc;
         c.split_ext = std::get<3>(kv.first);
-        c.split_br = std::get<4>(kv.first);
         c.n = (int)kv.second.size();
         for (int32_t m : kv.second) {
             c.nb_sample = std::max(c.nb_sample, smp[m].nb);
             c.nb_items_ext = std::max(c.nb_items_ext, edge_ext[m].nb_items);
-            c.nb_items_br = std::max(c.nb_items_br, edge_br[m].nb_items);
             if (edge_ext[m].flat > 0) {
                 c.nb_flat = std::max(c.nb_flat, (int)flat_blocks(edge_ext[m]));
                 c.lds_flat = flat_lds_bytes(edge_ext[m]);
                 c.flat_waves = edge_ext[m].flat_waves;
             }
-            c.nb_bcheck = std::max<int>(c.nb_bcheck, (int)b->mem[m]->prm.batch);  // one wave each
+            c.nb_bridge = std::max(c.nb_bridge, (int)merge[m].blocks);
+            c.lds_bridge = std::max(c.lds_bridge, bridge_lds_bytes(merge[m]));
             c.lds = std::max(c.lds, scene_lds_bytes(b->mem[m]->sc));
             c.lds_sample = std::max(c.lds_sample, sample_lds_bytes(b->mem[m], nullptr));
         }

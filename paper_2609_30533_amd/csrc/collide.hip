@@ -496,7 +496,6 @@ EdgeArgs edge_args(const SceneDev &sc, const EdgeBufs &eb, int64_t E, const floa
     const int64_t want = (E + per_block - 1) / per_block;
     a.nb_items = (int)std::min<int64_t>(std::max<int64_t>(want, min_item_blocks), 8192);
     a.flat = a.flat_team = a.flat_waves = a.flat_w0 = 0;
-    a.skip_finish = 0;
     return a;
 }
 
@@ -545,18 +544,7 @@ hipError_t launch_edge_args(const EdgeArgs &a, hipStream_t s) {
         k_edge_items<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value, decltype(split)::value>
             <<<dim3(a.nb_items), dim3(256), lds, s>>>(a);
     });
-    if (!a.skip_finish) k_edge_finish<<<a.nb_edge, 256, 0, s>>>(a);
-    return hipGetLastError();
-}
-
-hipError_t launch_edge_items(const EdgeArgs &a, hipStream_t s) {
-    if (a.E <= 0) return hipSuccess;
-    if (a.E > a.eb.cap) return hipErrorInvalidValue;
-    const size_t lds = scene_lds_bytes(a.sc);
-    dispatch_split(a.sc, a.split_shift, [&](auto kind, auto ot, auto obs, auto split) {
-        k_edge_items<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value, decltype(split)::value>
-            <<<dim3(a.nb_items), dim3(256), lds, s>>>(a);
-    });
+    k_edge_finish<<<a.nb_edge, 256, 0, s>>>(a);
     return hipGetLastError();
 }
 

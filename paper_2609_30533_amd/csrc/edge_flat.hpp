@@ -5,6 +5,7 @@
 
 #include <algorithm>
 
+#include "pipeline.hpp"
 #include "st_internal.hpp"
 
 namespace st {
@@ -124,24 +125,28 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
-template <int KIND, int OT, int OBS, class Rows>
-__device__ __forceinline__ void edge_flat_body(const EdgeArgs &a, float4 *lds, int bx, Rows &&rows) {
-    const SceneDev &sc = a.sc;
+// One team's edges: the lane's edge e (lane < G; none from E on), G edges for
+// TW waves of the block, at most w0 states of an edge in the first phase, no
+// phase that starts at state `limit` or above.
+// rows(e, A, B) fills both endpoints, earlier time first, and returns false for
+// an edge not to check; done(e, n, hit, lo) gets, on the lanes of the team's
+// first wave that have an edge that was checked, its state count, its least hit
+// and the first state that was left to the caller (above n without a limit).
+template <int KIND, int OT, int OBS, class Rows, class Done>
+__device__ __forceinline__ void edge_flat_team(const SceneDev &sc, float4 *lds, int64_t E, int64_t e, int G, int TW,
+                                               int w0, int limit, Rows &&rows, Done &&done) {
     const int d = sc.d;
     const int wv = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63, nwv = blockDim.x >> 6;
-    const int G = a.flat, TW = a.flat_team;  // edges and waves of a team
     const int team = wv / TW, tw = wv - team * TW, teams = nwv / TW;
     float4 *s_row = lds + sc.lds_f4 + team * flat_team_f4(G);  // edge i: A at [4 i], B at [4 i + 2]
     int32_t *s_n = reinterpret_cast<int32_t *>(s_row + 4 * G), *s_hit = s_n + G;
     int32_t *s_map = reinterpret_cast<int32_t *>(lds + sc.lds_f4 + teams * flat_team_f4(G)) + 64 * wv;
-    const int64_t e = ((int64_t)bx * teams + team) * G + lane;  // the lane's edge
-    // the edges' rows first (rows(e, A, B) fills both endpoints, earlier
-    // time first, and returns false for an edge not to check), so that the
-    // producer's loads are in flight while other threads stage the scene;
-    // the staging's barrier also publishes the rows
+    // the edges' rows first, so that the producer's loads are in flight while
+    // other threads stage the scene; the staging's barrier also publishes the
+    // rows
     int32_t n_own = -1;
     if (tw == 0 && lane < G) {
-        if (e < a.E) {
+        if (e < E) {
             float A[kMaxDof + 1], B[kMaxDof + 1];
             if (rows(e, A, B)) {
                 n_own = edge_states(A, B, d, sc.v_d, sc.h_d);
@@ -156,13 +161,13 @@ __device__ __forceinline__ void edge_flat_body(const EdgeArgs &a, float4 *lds, i
     }
     stage_obstacles(sc, lds);
     if (tw != 0 && lane < G) n_own = s_n[lane];
-    int lo = 0, width = a.flat_w0;
+    int lo = 0, width = w0;
     int32_t hit_own;
     for (;;) {
         // the phase's states of the lane's edge and their place
         hit_own = lane < G ? __atomic_load_n(&s_hit[lane], __ATOMIC_RELAXED) : 0;
         const int left = n_own - lo + 1;  // (an edge not to check has n = -1)
-        const int c = lane < G && hit_own == kNoHit && left > 0 ? min(left, width) : 0;
+        const int c = lane < G && hit_own == kNoHit && left > 0 && lo < limit ? min(left, width) : 0;
         const int incl = wave_scan(c, 0, [](int x, int y) { return x + y; });
         const int off = incl - c, T = __builtin_amdgcn_readlane(incl, 63);
         const int m = __popcll(__ballot(c > 0));
@@ -204,17 +209,26 @@ __device__ __forceinline__ void edge_flat_body(const EdgeArgs &a, float4 *lds, i
         // at least four times as wide, and half a state per lane
         width = min(kFlatMaxWidth, max(4 * width, 32 * TW / m));
     }
-    // results and work counters
-    if (tw != 0) return;
+    if (tw == 0 && lane < G && n_own >= 0) done(e, n_own, hit_own, lo);
+}
+
+// A block's consecutive edges of an edge list: free / first hit, work counters.
+template <int KIND, int OT, int OBS, class Rows>
+__device__ __forceinline__ void edge_flat_body(const EdgeArgs &a, float4 *lds, int bx, Rows &&rows) {
+    const int G = a.flat, TW = a.flat_team;
+    const int wv = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int team = wv / TW, teams = (int)(blockDim.x >> 6) / TW;
+    const int64_t e = ((int64_t)bx * teams + team) * G + lane;
     unsigned long long states = 0, edges = 0;
-    if (lane < G && e < a.E && n_own >= 0) {
-        const bool fr = hit_own == kNoHit;
+    edge_flat_team<KIND, OT, OBS>(a.sc, lds, a.E, e, G, TW, a.flat_w0, INT32_MAX, rows,
+                                  [&](int64_t e, int32_t n, int32_t hit, int32_t) {
+        const bool fr = hit == kNoHit;
         a.free_out[e] = fr ? 1 : 0;
-        if (a.first_hit) a.first_hit[e] = fr ? -1 : hit_own;
-        states = fr ? (unsigned long long)n_own + 1ull : (unsigned long long)hit_own + 1ull;
+        if (a.first_hit) a.first_hit[e] = fr ? -1 : hit;
+        states = fr ? (unsigned long long)n + 1ull : (unsigned long long)hit + 1ull;
         edges = 1;
-    }
-    if (a.work) {
+    });
+    if (a.work && wv == team * TW) {
         for (int o = 32; o > 0; o >>= 1) {
             states += __shfl_down(states, o, 64);
             edges += __shfl_down(edges, o, 64);
@@ -261,6 +275,35 @@ inline void flat_shape_extension(EdgeArgs &a, int number) {
 // mixed batch of 128 problems: 378 us per iteration; 404 with 32 edges and
 // eight waves, 438 with a wave per 8 edges).
 inline void flat_shape_batch(EdgeArgs &a) { flat_set(a, 8, 4, 4, 64); }
+
+// The bridge check.  One problem: its advanced workers over 256 blocks of eight
+// waves (one block per CU: two do not fit the registers), first phases of 32
+// states per wave (most bridges that collide do so within a few states, and a
+// narrow phase gives each state several lanes); what is undecided when a phase
+// would start at state 128 or above goes to the spread-out check, so that a
+// few long bridges do not hold up one block.  6-DOF arm at 4096 samples, five
+// problems: 88 to 136 us per iteration; 99 to 140 with one wave and 64 states per
+// bridge and chunks of the rest, 86 to 133 (but 115 for 109) with 512 blocks and
+// no limit; 7-DOF arm at 8192: 182 to 343; 186 to 354; 196 to 351.  A batch
+// member: a block per four samples, no limit (its launch would be one more for
+// every scene class): mixed batch of 128 341 us with eight waves per block, 358
+// with four, 348 with a limit of 512, 390 with chunks.
+constexpr int kBridgeBlocks = 256, kBridgeW0 = 32, kBridgeLimit = 128, kBridgeSamplesBatch = 4;
+inline void bridge_shape(BridgeArgs &a) {
+    a.blocks = (int)std::max<int64_t>((a.B + kFlatMaxEdges - 1) / kFlatMaxEdges, std::min<int64_t>(kBridgeBlocks, a.B));
+    a.w0 = kBridgeW0;
+    a.limit = kBridgeLimit;
+}
+inline void bridge_shape_batch(BridgeArgs &a) {
+    a.blocks = (int)((a.B + kBridgeSamplesBatch - 1) / kBridgeSamplesBatch);
+    a.w0 = kBridgeW0;
+    a.limit = INT32_MAX;
+}
+// Its dynamic LDS behind the scene: the team's and one word per edge.
+inline size_t bridge_lds_bytes(const BridgeArgs &a) {
+    const int G = (int)((a.B + a.blocks - 1) / a.blocks);
+    return flat_lds_bytes(kFlatWaves, kFlatWaves, G) + (size_t)G * sizeof(uint32_t);
+}
 
 inline int64_t flat_blocks(const EdgeArgs &a) {
     const int64_t per = (int64_t)a.flat * (a.flat_waves / a.flat_team);

@@ -1245,152 +1245,164 @@ __global__ __launch_bounds__(1024) void k_insert(InsertArgs a0, const InsertArgs
 // ---------------------------------------------------------------------------
 
 
-// Bridge selection's merge and the first states of the bridge edge in one
-// launch, one wave per advanced worker, given densely (wave i takes the i-th
-// worker of the bridge buckets, so the waves that check are packed into
-// the first blocks and no SIMD holds more than one of them): the wave merges
-// its worker's per-slice candidates (the lexicographic (key, index) minimum
-// over the slices: arrival, then rho, then node index), then checks
-// states 0 .. 63 of the chosen bridge edge (lane j takes state j, the FIRST
-// rule over the wave), which decides every bridge that collides there or has
-// at most 64 states.  The rest (no hit among 64 or more states) append their
-// work items to the rank lists for the item kernel, which checks them whole.
-// Wave i also writes the empty bridge of worker i when that worker did not
-// advance.  The per-edge records (state count, least hit) are the plan
-// step's; the finish step runs in the publish kernel.
+// Bridge selection's merge and the bridge edges' check in one launch.  The
+// advanced workers are given densely (the bridge buckets); every block takes
+// G = ceil(workers / blocks) of them, merges each one's per-slice candidates
+// (the lexicographic (key, index) minimum over the slices: arrival, then rho,
+// then node index) and checks the chosen bridges (x_new, y), all its waves as one
+// team (edge_flat_team), up to the limit; bridges undecided there go to the rest
+// list.  Worker i without a bridge gets its empty record here, and every other
+// its state count and least hit; free flags and work counters are formed in the
+// publish kernel.
 template <int KIND, int OT, int OBS, bool MULTI>
-__global__ __launch_bounds__(256) void k_bridge_check(BridgeArgs a0, EdgeArgs ea0, const BridgeArgs *__restrict__ av,
-                                                      const EdgeArgs *__restrict__ ev,
-                                                      const int32_t *__restrict__ members) {
+__global__ __launch_bounds__(64 * kFlatWaves) void k_bridge_check(BridgeArgs a0, const BridgeArgs *__restrict__ av,
+                                                                 const int32_t *__restrict__ members) {
     extern __shared__ float4 lds[];
-    // many problems per launch: the member is blockIdx.x, so that members
-    // vary fastest and every member's first blocks (the ones that check) are
-    // dispatched ahead of the members' empty blocks; blocks past the
-    // member's own grid leave
+    // many problems per launch: the member is blockIdx.x, its blocks blockIdx.y
     const int bx = MULTI ? (int)blockIdx.y : (int)blockIdx.x;
-    const int mi = MULTI ? members[blockIdx.x] : 0;
-    const BridgeArgs &a = MULTI ? av[mi] : a0;
-    const EdgeArgs &ea = MULTI ? ev[mi] : ea0;
-    if (MULTI && (int64_t)bx * (blockDim.x >> 6) >= a.B) return;
-    const int lane = threadIdx.x & 63;
-    const int64_t i = ((int64_t)bx * blockDim.x + threadIdx.x) >> 6;
+    const BridgeArgs &a = MULTI ? av[members[blockIdx.x]] : a0;
+    const int nblk = a.blocks;
+    if (MULTI && bx >= nblk) return;
+    const int lane = threadIdx.x & 63, wv = uniform(threadIdx.x >> 6), waves = blockDim.x >> 6;
     const Work &k = a.w;
-    const SceneDev &sc = ea.sc;
-    const EdgeBufs &eb = ea.eb;
+    const SceneDev &sc = a.sc;
     const int d = a.tree.d, W = d + 1;
-    if (i < a.B && lane == 0 && k.status[i] != ST_STATUS_ADVANCED) {
-        k.bridge[i] = -1;
-        k.br_valid[i] = 0;
-        k.Up[i] = INFINITY;
-        k.Cp[i] = INFINITY;
-        eb.n[i] = -1;
-    }
-    const int32_t nb0 = k.bcnt[kBcntBridge], nb1 = k.bcnt[kBcntBridge + 1];
-    const int64_t nsel = (int64_t)nb0 + nb1;
+    auto empty = [&](int64_t w) {
+        k.bridge[w] = -1;
+        k.br_valid[w] = 0;
+        k.Up[w] = INFINITY;
+        k.Cp[w] = INFINITY;
+        a.n[w] = -1;
+    };
+    for (int64_t w = (int64_t)bx * blockDim.x + threadIdx.x; w < a.B; w += (int64_t)nblk * blockDim.x)
+        if (k.status[w] != ST_STATUS_ADVANCED) empty(w);
+    const int32_t nb0 = uniform(k.bcnt[kBcntBridge]), nb1 = uniform(k.bcnt[kBcntBridge + 1]);
+    const int nsel = nb0 + nb1, G = (nsel + nblk - 1) / nblk;
     // a block past the advanced workers has nothing more to do (whole block)
-    if ((int64_t)bx * (blockDim.x >> 6) >= nsel) return;
-    const bool in = i < nsel;
-    const int64_t w = in ? (i < nb0 ? k.border_br[i] : k.border_br[a.B + (i - nb0)]) : 0;
-    unsigned long long bk = kNoKey;
-    uint32_t bi = 0xffffffffu;
-    if (in) {
-        for (int y = lane; y < a.nch; y += 64) {
-            const int32_t ii = k.br_idx[i * a.nch + y];
-            if (ii < 0) continue;
-            const unsigned long long kk = k.br_key[i * a.nch + y];
-            if (kk < bk || (kk == bk && (uint32_t)ii < bi)) {
-                bk = kk;
-                bi = (uint32_t)ii;
+    if ((int64_t)bx * G >= nsel) return;
+    const int i0 = bx * G, cnt = min(G, nsel - i0);
+    // the candidates of edge g: `sub` lanes each (a power of two), all groups
+    // of lanes at once; the result goes to the LDS word of the edge
+    uint32_t *s_best = reinterpret_cast<uint32_t *>(lds + sc.lds_f4 + flat_team_f4(G)) + 64 * waves;
+    const int sub = a.merge_lanes, per = 64 / sub, ls = lane & (sub - 1);
+    for (int g0 = wv * per; g0 < cnt; g0 += waves * per) {
+        const int g = g0 + lane / sub;
+        unsigned long long bk = kNoKey;
+        uint32_t bi = 0xffffffffu;
+        if (g < cnt) {
+            for (int y = ls; y < a.nch; y += sub) {
+                const int64_t r = (int64_t)(i0 + g) * a.nch + y;
+                const int32_t ii = k.br_idx[r];
+                const unsigned long long kk = k.br_key[r];
+                if (ii >= 0 && (kk < bk || (kk == bk && (uint32_t)ii < bi))) {
+                    bk = kk;
+                    bi = (uint32_t)ii;
+                }
             }
         }
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long ok = __shfl_xor(bk, o, 64);
-        const uint32_t oi = __shfl_xor(bi, o, 64);
-        if (ok < bk || (ok == bk && oi < bi)) {
-            bk = ok;
-            bi = oi;
+        for (int o = sub >> 1; o > 0; o >>= 1) {
+            const unsigned long long ok = __shfl_xor(bk, o, 64);
+            const uint32_t oi = __shfl_xor(bi, o, 64);
+            if (ok < bk || (ok == bk && oi < bi)) {
+                bk = ok;
+                bi = oi;
+            }
         }
+        if (g < cnt && ls == 0) s_best[g] = bi;
     }
-    const bool has = in && bi != 0xffffffffu;  // the same on every lane of the wave
-    // the bridge's rows in flight while the block stages the scene
-    float y[kMaxDof + 1], xn[kMaxDof + 1];
-    float up = 0.f, cp = 0.f, cb = 0.f;
-    if (has) {
+    __syncthreads();
+    // worker of the lane's edge
+    const int64_t i = i0 + lane;
+    const bool in = wv == 0 && lane < cnt;
+    const int64_t w = in ? (i < nb0 ? k.border_br[i] : k.border_br[a.B + (i - nb0)]) : 0;
+    edge_flat_team<KIND, OT, OBS>(
+        sc, lds, nsel, i, G, waves, max(1, a.w0 * waves / G), a.limit,
+        [&](int64_t, float (&A)[kMaxDof + 1], float (&B)[kMaxDof + 1]) {
+            const uint32_t bi = s_best[lane];
+            if (bi == 0xffffffffu) {
+                empty(w);
+                return false;
+            }
+            float y[kMaxDof + 1], xn[kMaxDof + 1];
 #pragma unroll
-        for (int j = 0; j < kMaxDof; ++j) {
-            y[j] = j < d ? a.tree.x[(int64_t)j * a.tree.total + bi] : 0.f;
-            xn[j] = j < d ? k.xnew[w * W + j] : 0.f;
-        }
-        y[kMaxDof] = a.tree.x[(int64_t)d * a.tree.total + bi];
-        xn[kMaxDof] = k.xnew[w * W + d];
-        up = a.dir[w] == 0 ? a.tree.rootT[bi] : k.rootT_new[w];
-        cp = k.cost_new[w];
-        cb = a.tree.cost[bi];
-    }
+            for (int j = 0; j < kMaxDof; ++j) {
+                y[j] = j < d ? a.tree.x[(int64_t)j * a.tree.total + bi] : 0.f;
+                xn[j] = j < d ? k.xnew[w * W + j] : 0.f;
+            }
+            y[kMaxDof] = a.tree.x[(int64_t)d * a.tree.total + bi];
+            xn[kMaxDof] = k.xnew[w * W + d];
+            const float up = a.dir[w] == 0 ? a.tree.rootT[bi] : k.rootT_new[w];
+            const float cp = k.cost_new[w], cb = a.tree.cost[bi];
+            float D2 = 0.f;
+#pragma unroll
+            for (int j = 0; j < kMaxDof; ++j) {
+                if (j < d) {
+                    const float e = y[j] - xn[j];
+                    D2 = fmaf(e, e, D2);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kMaxDof; ++j)
+                if (j < d) k.xb[w * W + j] = y[j];
+            k.xb[w * W + d] = y[kMaxDof];
+            k.bridge[w] = (int32_t)bi;
+            k.br_valid[w] = 1;
+            k.Up[w] = up;
+            k.Cp[w] = cp + sqrtf(D2) + cb;
+            // the edge (x_new, y), earlier time first
+            const bool sw = xn[kMaxDof] > y[kMaxDof];
+#pragma unroll
+            for (int j = 0; j <= kMaxDof; ++j) {
+                A[j] = sw ? y[j] : xn[j];
+                B[j] = sw ? xn[j] : y[j];
+            }
+            return true;
+        },
+        [&](int64_t, int32_t n, int32_t hit, int32_t lo) {
+            a.n[w] = n;
+            a.hit[w] = hit;
+            if (hit == kNoHit && lo <= n) a.rest[atomicAdd(&k.bcnt[kBcntBridge + 2], 1)] = make_int2((int)w, lo);
+        });
+}
+
+// The long bridges' remaining states, spread over the whole launch: every wave
+// works by itself on one edge's states, 64 at a time, the waves of an edge
+// interleaved.  A wave stops at a hit below its states (hits merge with an
+// atomic minimum), so the least colliding index is exact.
+template <int KIND, int OT, int OBS>
+__global__ __launch_bounds__(64 * kFlatWaves) void k_bridge_rest(BridgeArgs a) {
+    extern __shared__ float4 lds[];
+    const int bx = blockIdx.x, nblk = gridDim.x, waves = blockDim.x >> 6;
+    const int R = uniform(a.w.bcnt[kBcntBridge + 2]);
+    const int total = nblk * waves;
+    // wave id: blocks vary fastest, so that few edges spread over all CUs
+    const int id = uniform(threadIdx.x >> 6) * nblk + bx;
+    const int per = max(1, total / max(R, 1));  // waves per edge
+    // a block whose first wave has no edge has none at all (whole block)
+    if (bx >= R * per) return;
+    const SceneDev &sc = a.sc;
     stage_obstacles(sc, lds);
-    if (!in) return;  // whole waves, after the block's barrier
-    if (!has) {
-        if (lane == 0) {
-            k.bridge[w] = -1;
-            k.br_valid[w] = 0;
-            k.Up[w] = INFINITY;
-            k.Cp[w] = INFINITY;
-            eb.n[w] = -1;
+    const int lane = threadIdx.x & 63, d = a.tree.d;
+    for (int u = id; u < R * per; u += total) {
+        const int r = u % R, part = u / R;
+        const int2 it = a.rest[r];
+        const int64_t w = uniform(it.x);
+        float A[kMaxDof + 1], B[kMaxDof + 1];
+        load_edge_rows(a.w.xnew, a.w.xb, w, d, A, B);
+        const int n = uniform(a.n[w]);
+        for (int base = uniform(it.y) + 64 * part; base <= n; base += 64 * per) {
+            if (uniform(__atomic_load_n(&a.hit[w], __ATOMIC_RELAXED)) < base) break;
+            const int j = base + lane;
+            float q[kMaxDof];
+            float t;
+            edge_state(A, B, min(j, n), n, q, t);
+            const bool hit = state_hits<KIND, OT, OBS, true>(sc, lds, q, t, j <= n, ~0ull, (1ull << lane) - 1ull);
+            const uint64_t hm = __ballot(hit && j <= n);
+            if (hm) {
+                if (lane == 0) atomicMin(&a.hit[w], base + (int)__builtin_ctzll(hm));
+                break;
+            }
         }
-        return;
-    }
-    float D2 = 0.f;
-#pragma unroll
-    for (int j = 0; j < kMaxDof; ++j) {
-        if (j < d) {
-            const float e = y[j] - xn[j];
-            D2 = fmaf(e, e, D2);
-        }
-    }
-    if (lane == 0) {
-#pragma unroll
-        for (int j = 0; j < kMaxDof; ++j)
-            if (j < d) k.xb[w * W + j] = y[j];
-        k.xb[w * W + d] = y[kMaxDof];
-        k.bridge[w] = (int32_t)bi;
-        k.br_valid[w] = 1;
-        k.Up[w] = up;
-        k.Cp[w] = cp + sqrtf(D2) + cb;
-    }
-    // the edge (x_new, y), earlier time first, and its state count
-    float A[kMaxDof + 1], B[kMaxDof + 1];
-    const bool sw = xn[kMaxDof] > y[kMaxDof];
-#pragma unroll
-    for (int j = 0; j <= kMaxDof; ++j) {
-        A[j] = sw ? y[j] : xn[j];
-        B[j] = sw ? xn[j] : y[j];
-    }
-    const int32_t n = edge_states(A, B, d, sc.v_d, sc.h_d);
-    const bool act = lane <= n;
-    float q[kMaxDof];
-    float t = 0.f;
-    if (act) {
-        edge_state(A, B, lane, n, q, t);
-    } else {
-#pragma unroll
-        for (int j = 0; j < kMaxDof; ++j) q[j] = 0.f;
-    }
-    const bool hit = state_hits<KIND, OT, OBS, true>(sc, lds, q, t, act, ~0ull, (1ull << lane) - 1ull);
-    const uint64_t hm = __ballot(hit && act);
-    if (lane == 0) {
-        eb.n[w] = n;
-        eb.hit[w] = hm ? (int32_t)__builtin_ctzll(hm) : kNoHit;
-    }
-    if (hm || n < 64) return;  // decided
-    // undecided: the whole edge goes to the item kernel (L states per chunk,
-    // up to mmax items), one rank-list append per item
-    const int L = 1 << (ea.lpe_shift - ea.split_shift);
-    const int64_t c = ((int64_t)n + L) / L;
-    const int m = (int)(c < eb.mmax ? c : eb.mmax);
-    if (lane < m) {
-        const int slot = atomicAdd(&eb.cnt[lane * kCntStride], 1);
-        eb.items[(int64_t)lane * eb.cap + slot] = make_int2((int)w, lane);
     }
 }
 
@@ -1603,10 +1615,8 @@ __global__ __launch_bounds__(1024) void k_publish(PublishArgs a0, const PublishA
         atomicAdd(&a.work_br[0], edges);
         atomicAdd(&a.work_br[1], states);
     }
-    // the rank lists of the edge pipeline and the bridge buckets are consumed:
-    // empty for the next launch
-    if (tid < a.eb.mmax) a.eb.cnt[tid * kCntStride] = 0;
-    if (tid < 2) k.bcnt[kBcntBridge + tid] = 0;
+    // the bridge buckets are consumed: empty for the next launch
+    if (tid < 3) k.bcnt[kBcntBridge + tid] = 0;
     // optional caller outputs (a candidate that is not a free bridge of an
     // advanced worker reports U = C = infinity)
     const st_extend_out &o = a.out;
@@ -1843,7 +1853,7 @@ void work_free(st_problem *p) {
     Work &w = p->work;
     void *bufs[] = {w.dir, w.flags, w.grp, w.T, w.qr, w.tr, w.nn_key, w.tiles, w.n_tiles, w.bcnt, w.border_nn,
                     w.border_br, w.xn, w.xnew, w.edge_valid, w.edge_free, w.first_hit, w.status, w.parent, w.new_idx, w.cost_new,
-                    w.rootT_new, w.br_key, w.br_idx, w.bridge, w.xb, w.br_valid, w.br_free, w.Up, w.Cp};
+                    w.rootT_new, w.br_key, w.br_idx, w.bridge, w.xb, w.br_valid, w.Up, w.Cp};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     memset(&w, 0, sizeof w);
@@ -1888,12 +1898,10 @@ int work_reserve(st_problem *p, int64_t B) {
     ST_HIP(dalloc(&w.bridge, B));
     ST_HIP(dalloc(&w.xb, (size_t)B * W));
     ST_HIP(dalloc(&w.br_valid, B));
-    ST_HIP(dalloc(&w.br_free, B));
     ST_HIP(dalloc(&w.Up, B));
     ST_HIP(dalloc(&w.Cp, B));
     ST_HIP(hipMemset(w.bcnt, 0, kBcntSize * sizeof(int32_t)));
     ST_HIP(hipMemset(w.edge_free, 0, B));
-    ST_HIP(hipMemset(w.br_free, 0, B));
     return ST_OK;
 }
 
@@ -1967,7 +1975,6 @@ int sample_batch(st_problem *p, int64_t iter, int64_t B, const st_samples &out, 
     return ST_OK;
 }
 
-static int edge_shift(const st_problem *p, bool bridge) { return bridge ? p->tune_br : p->tune_ext; }
 
 void make_iter_args(const st_problem *p, int64_t B, const st_samples &in, const st_extend_out *out, int nch_nn,
                     int nch_br, int min_item_blocks, int64_t launch_edges, IterArgs &a) {
@@ -2018,7 +2025,7 @@ void make_iter_args(const st_problem *p, int64_t B, const st_samples &in, const 
     ta.w = w;
     // extension edge checks (a4)
     a.edge_ext = edge_args(p->sc, p->ebufs, B, w.xn, w.xnew, w.edge_valid, w.edge_free, w.first_hit,
-                           edge_shift(p, false), p->d_plan->work, min_item_blocks,
+                           p->tune_ext, p->d_plan->work, min_item_blocks,
                            split_for(p->split_ext, launch_edges));
     // extension edges are short (rho <= eta: at most ceil(sqrt(2) eta / h) + 1
     // states): the flattened path, unless eta / h is unusually large
@@ -2056,9 +2063,13 @@ void make_iter_args(const st_problem *p, int64_t B, const st_samples &in, const 
     ba.nch = nch_br;
     ba.dir = in.dir;
     ba.w = w;
-    a.edge_br = edge_args(p->sc, p->ebufs, B, w.xnew, w.xb, w.br_valid, w.br_free, w.first_hit, edge_shift(p, true),
-                          p->d_plan->work + 2, min_item_blocks, split_for(p->split_br, launch_edges));
-    a.edge_br.skip_finish = 1;  // k_publish reads the bridge hits itself
+    ba.sc = p->sc;
+    ba.merge_lanes = 1;
+    while (ba.merge_lanes < 64 && ba.merge_lanes < nch_br) ba.merge_lanes *= 2;
+    ba.n = p->ebufs.n;
+    ba.hit = p->ebufs.hit;
+    ba.rest = p->ebufs.items;
+    bridge_shape(ba);
     // publish (a7)
     PublishArgs &pb = a.publish;
     pb.pl = p->d_plan;
@@ -2129,17 +2140,17 @@ int extend_batch(st_problem *p, int64_t B, const st_samples &in, const st_extend
     prof_mark(p, kStBridgeSel, s);
     k_scan<kScanBridge, false><<<dim3(a.mt_br, a.scan_br.nch), kTileQ, 0, s>>>(a.scan_br, nullptr, nullptr);
     ST_HIP(hipGetLastError());
-    // the merge and the first 64 states of every bridge edge in one launch
-    // (its stage timing counts it as the bridge check), then the item kernel
-    // for the undecided rest
+    // the merge and the bridge edges' check in one launch (the stage timing
+    // counts it as the bridge check)
     prof_mark(p, kStBridgeEdge, s);
     dispatch_scene_edges(p->sc, [&](auto kind, auto ot, auto obs) {
         k_bridge_check<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value, false>
-            <<<(int)((B * 64 + 255) / 256), 256, scene_lds_bytes(p->sc), s>>>(a.merge, a.edge_br, nullptr, nullptr,
-                                                                             nullptr);
+            <<<a.merge.blocks, 64 * kFlatWaves, scene_lds_bytes(p->sc) + bridge_lds_bytes(a.merge), s>>>(
+                a.merge, nullptr, nullptr);
+        k_bridge_rest<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value>
+            <<<a.merge.blocks, 64 * kFlatWaves, scene_lds_bytes(p->sc), s>>>(a.merge);
     });
     ST_HIP(hipGetLastError());
-    ST_HIP(launch_edge_items(a.edge_br, s));
     prof_mark(p, kStPublish, s);
     k_publish<false><<<1, 1024, 0, s>>>(a.publish, nullptr, a.roots, nullptr);
     ST_HIP(hipGetLastError());
@@ -2194,19 +2205,15 @@ int launch_batch_iteration(const BatchLaunch &L, hipStream_t s) {
     }
     k_insert<true><<<dim3(L.max_pools, L.P), L.ins_threads, 0, s>>>(InsertArgs{}, L.insert);
     scan_launch(IC<kScanBridge>{}, L.mt_br, L.P, L.all_members, L.scan_br);
-    // the merge and the first 64 states of every bridge edge, per scene
-    // class, then the item kernel for the undecided rest; one wave per block
-    // (a member's blocks past its advanced workers leave before staging, and
-    // a checking wave does not wait for three others to be scheduled)
+    // the merge and the bridge edges' check, per scene class
     for (const BatchClass &c : L.classes) {
         dispatch_scene_edges(c.key, [&](auto kind, auto ot, auto obs) {
             k_bridge_check<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value, true>
-                <<<dim3(c.n, c.nb_bcheck), 64, c.lds, s>>>(BridgeArgs{}, EdgeArgs{}, L.merge, L.edge_br, c.members);
+                <<<dim3(c.n, c.nb_bridge), 64 * kFlatWaves, c.lds + c.lds_bridge, s>>>(BridgeArgs{}, L.merge,
+                                                                                             c.members);
         });
         ST_HIP(hipGetLastError());
     }
-    for (const BatchClass &c : L.classes)
-        ST_HIP(launch_edge_items_multi(c.key, c.split_br, L.edge_br, c.members, c.n, c.nb_items_br, c.lds, s));
     k_publish<true><<<dim3(1, L.P), 1024, 0, s>>>(PublishArgs{}, L.publish, RootsArgs{}, L.roots);
     ST_HIP(hipGetLastError());
     return ST_OK;

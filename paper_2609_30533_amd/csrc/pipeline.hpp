@@ -81,11 +81,18 @@ struct InsertArgs {
 };
 
 struct BridgeArgs {
+    SceneDev sc;
     TreeDev tree;
     int64_t B;
     int32_t nch;
+    int32_t merge_lanes;  // lanes that merge one worker's candidates (a power of two)
+    int32_t blocks;       // blocks that share the advanced workers out (at least B / 64)
+    int32_t w0;           // states per wave in the first phase
     const int8_t *dir;
-    Work w;  // the bridge buckets give the advanced workers (one wave each, densely)
+    Work w;               // the bridge buckets give the advanced workers, densely
+    int32_t limit;        // states from here on are left to the spread-out check
+    int32_t *n, *hit;     // per worker: states of its bridge edge (-1 without), least hit
+    int2 *rest;           // (worker, first state left) of long bridges, bcnt[kBcntBridge + 2] of them
 };
 
 struct PublishArgs {
@@ -113,7 +120,7 @@ struct IterArgs {
     PrepArgs prep_nn;
     ScanArgs scan_nn, scan_br;
     SteerArgs steer;
-    EdgeArgs edge_ext, edge_br;
+    EdgeArgs edge_ext;
     InsertArgs insert;
     BridgeArgs merge;
     PublishArgs publish;
@@ -134,12 +141,13 @@ void make_iter_args(const st_problem *p, int64_t B, const st_samples &in, const 
 // obstacle tile, obstacle-time mode, lanes per state).
 struct BatchClass {
     SceneDev key;           // kind, ot and obs_mode select the instance
-    int split_ext, split_br;  // lanes per state (log2) of the two edge launches
+    int split_ext;          // lanes per state (log2) of the chunked extension check
     const int32_t *members; // device: record indices
     int n;                  // members
-    int nb_sample, nb_items_ext, nb_items_br, nb_flat, nb_bcheck;  // grid maxima over the members
+    int nb_sample, nb_items_ext, nb_flat, nb_bridge;  // grid maxima over the members
     size_t lds;             // dynamic LDS, maximum over the members
     size_t lds_flat;        // the extension check's, behind the scene
+    size_t lds_bridge;      // the bridge check's, behind the scene
     int flat_waves;         // and its waves per block (the same for every member)
     size_t lds_sample;      // the sampler's (scene and guided windows), maximum over the members
 };
@@ -154,7 +162,7 @@ struct BatchLaunch {
     const SampleArgs *sample = nullptr;
     const ScanArgs *scan_nn = nullptr, *scan_br = nullptr;
     const SteerArgs *steer = nullptr;
-    const EdgeArgs *edge_ext = nullptr, *edge_br = nullptr;
+    const EdgeArgs *edge_ext = nullptr;
     const InsertArgs *insert = nullptr;
     const BridgeArgs *merge = nullptr;
     const PublishArgs *publish = nullptr;

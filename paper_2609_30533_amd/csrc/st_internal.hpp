@@ -124,7 +124,6 @@ struct EdgeArgs {
     // one-kernel path: edges per team (0: chunked path), waves per team and per
     // block, width of the first phase
     int32_t flat, flat_team, flat_waves, flat_w0;
-    int32_t skip_finish;        // 1: the consumer of the results does the finish step itself
 };
 
 // Per-batch work buffers (capacity Bcap workers).
@@ -156,7 +155,7 @@ struct Work {
     int32_t *br_idx;             // [B][nch]
     int32_t *bridge;
     float *xb;                   // [B][d+1]
-    uint8_t *br_valid, *br_free;
+    uint8_t *br_valid;
     float *Up, *Cp;
 };
 
@@ -204,7 +203,7 @@ struct st_problem {
     // lanes per edge chunk (log2) for extension, bridge and st_check_edges launches
     int tune_ext = 5, tune_br = 4, tune_api = 5;
     // lanes per state (log2) for the same three launches; -1 chooses by size
-    int split_ext = -1, split_br = -1, split_api = -1;
+    int split_ext = -1, split_api = -1;
     // st_check_edges takes the chunked path when the caller chose its lanes
     bool api_lanes = false, api_split = false;
     // a quarter of the extension edges per block of the one-kernel path (0: chunked item path)
@@ -267,7 +266,6 @@ EdgeArgs edge_args(const SceneDev &sc, const EdgeBufs &eb, int64_t E, const floa
 hipError_t launch_edge_args(const EdgeArgs &a, hipStream_t s);
 // The item kernel alone, for edges whose records (state count, least hit)
 // and work items another kernel has written (the bridge check).
-hipError_t launch_edge_items(const EdgeArgs &a, hipStream_t s);
 // The same pipeline for P problems at once (records in device memory); the
 // item kernel runs once per scene class over its member records.
 hipError_t launch_edge_plan_multi(const EdgeArgs *d_args, int P, int max_nb_edge, hipStream_t s);
