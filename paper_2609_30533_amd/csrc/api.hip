@@ -514,6 +514,8 @@ static int init_state(st_problem *p) {
     ST_HIP(launch_init_state(p));
     ST_HIP(hipStreamSynchronize(nullptr));
     p->iter = 0;
+    p->nodes_known = p->tree.n_pools;
+    p->nodes_iter = 0;
     return ST_OK;
 }
 
@@ -1003,6 +1005,9 @@ int st_tree_import(st_problem *p, const int64_t *counts, const float *x, const i
         }
     }
     ST_HIP(hipMemcpy(p->d_plan, &pl, sizeof pl, hipMemcpyHostToDevice));
+    p->nodes_known = 0;
+    for (int i = 0; i < T.n_pools; ++i) p->nodes_known += counts[i];
+    p->nodes_iter = iter;
     return ST_OK;
 }
 

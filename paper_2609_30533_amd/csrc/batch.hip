@@ -165,6 +165,7 @@ static int batch_build(st_batch *b) {
         L.nb_edge = std::max(L.nb_edge, a.edge_ext.nb_edge);
         L.max_pools = std::max(L.max_pools, p->tree.n_pools);
         L.ins_threads = std::max(L.ins_threads, insert_threads(B));
+        L.filter = L.filter || scan_may_filter(B, p->tree.total);
         L.ext_flat = L.ext_flat && a.edge_ext.flat > 0;
         const std::vector<void *> sb = member_bufs(p);
         b->saved_bufs.insert(b->saved_bufs.end(), sb.begin(), sb.end());

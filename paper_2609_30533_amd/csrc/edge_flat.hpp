@@ -287,7 +287,7 @@ inline void flat_shape_batch(EdgeArgs &a) { flat_set(a, 8, 4, 4, 64); }
 // no limit; 7-DOF arm at 8192: 182 to 343; 186 to 354; 196 to 351.  A batch
 // member: a block per four samples, no limit (its launch would be one more for
 // every scene class): mixed batch of 128 341 us with eight waves per block, 358
-// with four, 348 with a limit of 512, 390 with chunks.
+// with four, 348 with a limit of 512, 390 with chunks (all with the scans of then).
 constexpr int kBridgeBlocks = 256, kBridgeW0 = 32, kBridgeLimit = 128, kBridgeSamplesBatch = 4;
 inline void bridge_shape(BridgeArgs &a) {
     a.blocks = (int)std::max<int64_t>((a.B + kFlatMaxEdges - 1) / kFlatMaxEdges, std::min<int64_t>(kBridgeBlocks, a.B));

@@ -567,14 +567,18 @@ struct FilterQueries {
 // is fetched into registers while the current one is scanned.  TQ is 256, or
 // 64 for a batch of problems with at most 64 samples each: their tiles hold a
 // few queries, and one-wave blocks keep four times as many of the launch's
-// (mostly empty) blocks in flight.
-template <int MODE, bool MULTI, int TQ = kTileQ>
+// (mostly empty) blocks in flight.  FILTER instances hold the matrix-core path
+// too and decide on the device; it takes 144 registers and 24 KB of LDS where
+// the plain scan has 52 and 12, so launches that cannot reach its number of pairs
+// take the plain instance (1852 queries of 13771 nodes 29 us in the one, 26 in the
+// other).
+template <int MODE, bool MULTI, int TQ, bool FILTER>
 __global__ __launch_bounds__(TQ) void k_scan(ScanArgs a0, const ScanArgs *__restrict__ av,
                                              const int32_t *__restrict__ members) {
     __shared__ __align__(16) float sx[TQ][8];
     __shared__ float sT[TQ];
     __shared__ int32_t sI[TQ];
-    constexpr bool kFilter = MODE != kScanBridge && TQ == kTileQ;
+    constexpr bool kFilter = FILTER && MODE != kScanBridge && TQ == kTileQ;
     __shared__ bf16x8 s_op[kFilter ? 3 : 1][kFilter ? TQ : 1];  // the filter's operand rows, eight places apart
     __shared__ int s_wide[4];
     __shared__ int32_t s_pool[kMaxPools + 1], s_pre[kMaxPools + 1], s_cnt[kMaxPools + 1];
@@ -2091,6 +2095,27 @@ void make_iter_args(const st_problem *p, int64_t B, const st_samples &in, const 
     ra.no_recycling = p->prm.no_recycling;
 }
 
+// May a nearest-node launch of this many queries and nodes reach the filter?
+bool scan_may_filter(int64_t queries, int64_t nodes) { return queries * nodes >= kFilterMinPairs; }
+
+// Nodes of the problem's trees at most, for the choice of kernel instances (each
+// gives the same results at every size): what the host last wrote or read, and
+// two per worker of every iteration since.
+static int64_t nodes_bound(const st_problem *p) {
+    return std::min<int64_t>(p->tree.total,
+                             p->nodes_known + 2 * (int64_t)p->prm.batch * (p->iter - p->nodes_iter));
+}
+
+static void launch_scan(int metric, bool filter, dim3 grid, const ScanArgs &a, hipStream_t s) {
+    if (metric == ST_METRIC_RHO) {
+        if (filter) k_scan<kScanRho, false, kTileQ, true><<<grid, kTileQ, 0, s>>>(a, nullptr, nullptr);
+        else k_scan<kScanRho, false, kTileQ, false><<<grid, kTileQ, 0, s>>>(a, nullptr, nullptr);
+    } else {
+        if (filter) k_scan<kScanConfig, false, kTileQ, true><<<grid, kTileQ, 0, s>>>(a, nullptr, nullptr);
+        else k_scan<kScanConfig, false, kTileQ, false><<<grid, kTileQ, 0, s>>>(a, nullptr, nullptr);
+    }
+}
+
 int extend_batch(st_problem *p, int64_t B, const st_samples &in, const st_extend_out *out, hipStream_t s,
                  bool bucketed) {
     int rc = work_reserve(p, B);
@@ -2111,10 +2136,8 @@ int extend_batch(st_problem *p, int64_t B, const st_samples &in, const st_extend
         k_prep<<<1, 1024, 0, s>>>(a.prep_nn);
         ST_HIP(hipGetLastError());
     }
-    if (p->prm.variant == ST_INTERVAL_ROOT)
-        k_scan<kScanRho, false><<<dim3(a.mt_nn, a.scan_nn.nch), kTileQ, 0, s>>>(a.scan_nn, nullptr, nullptr);
-    else
-        k_scan<kScanConfig, false><<<dim3(a.mt_nn, a.scan_nn.nch), kTileQ, 0, s>>>(a.scan_nn, nullptr, nullptr);
+    launch_scan(p->prm.variant == ST_INTERVAL_ROOT ? ST_METRIC_RHO : ST_METRIC_CONFIG,
+                scan_may_filter(B, p->tree.total), dim3(a.mt_nn, a.scan_nn.nch), a.scan_nn, s);
     ST_HIP(hipGetLastError());
     if (a.edge_ext.flat) {
         // steering (a3) inside the extension check's launch (a4); the stage
@@ -2138,7 +2161,8 @@ int extend_batch(st_problem *p, int64_t B, const st_samples &in, const st_extend
     k_insert<false><<<p->tree.n_pools, insert_threads(B), 0, s>>>(a.insert, nullptr);
     ST_HIP(hipGetLastError());
     prof_mark(p, kStBridgeSel, s);
-    k_scan<kScanBridge, false><<<dim3(a.mt_br, a.scan_br.nch), kTileQ, 0, s>>>(a.scan_br, nullptr, nullptr);
+    k_scan<kScanBridge, false, kTileQ, false>
+        <<<dim3(a.mt_br, a.scan_br.nch), kTileQ, 0, s>>>(a.scan_br, nullptr, nullptr);
     ST_HIP(hipGetLastError());
     // the merge and the bridge edges' check in one launch (the stage timing
     // counts it as the bridge check)
@@ -2175,13 +2199,16 @@ int launch_batch_iteration(const BatchLaunch &L, hipStream_t s) {
         });
     }
     ST_HIP(hipGetLastError());
-    auto scan_multi = [&](auto mode, auto tq, int mt, int n, const int32_t *members, const ScanArgs *args) {
-        k_scan<decltype(mode)::value, true, decltype(tq)::value>
+    auto scan_multi = [&](auto mode, auto tq, auto filter, int mt, int n, const int32_t *members,
+                          const ScanArgs *args) {
+        k_scan<decltype(mode)::value, true, decltype(tq)::value, decltype(filter)::value>
             <<<dim3(mt, L.nch, n), decltype(tq)::value, 0, s>>>(ScanArgs{}, args, members);
     };
     auto scan_launch = [&](auto mode, int mt, int n, const int32_t *members, const ScanArgs *args) {
-        if (L.scan_tq == 64) scan_multi(mode, IC<64>{}, mt, n, members, args);
-        else scan_multi(mode, IC<kTileQ>{}, mt, n, members, args);
+        constexpr bool near = decltype(mode)::value != kScanBridge;
+        if (L.scan_tq == 64) scan_multi(mode, IC<64>{}, IC<0>{}, mt, n, members, args);
+        else if (near && L.filter) scan_multi(mode, IC<kTileQ>{}, IC<near>{}, mt, n, members, args);
+        else scan_multi(mode, IC<kTileQ>{}, IC<0>{}, mt, n, members, args);
     };
     if (L.n_ir > 0) scan_launch(IC<kScanRho>{}, L.mt_nn_ir, L.n_ir, L.ir_members, L.scan_nn);
     if (L.n_rr > 0) scan_launch(IC<kScanConfig>{}, L.mt_nn_rr, L.n_rr, L.rr_members, L.scan_nn);
@@ -2246,8 +2273,7 @@ int nearest_set(st_problem *p, int32_t set, int32_t metric, int32_t sigma, int64
     sa.n_tiles = w.n_tiles;
     sa.keys = w.nn_key;
     sa.nch = nch_for(nt);
-    if (metric == ST_METRIC_RHO) k_scan<kScanRho, false><<<dim3(nt, sa.nch), kTileQ, 0, s>>>(sa, nullptr, nullptr);
-    else k_scan<kScanConfig, false><<<dim3(nt, sa.nch), kTileQ, 0, s>>>(sa, nullptr, nullptr);
+    launch_scan(metric, scan_may_filter((int64_t)nt * kTileQ, nodes_bound(p)), dim3(nt, sa.nch), sa, s);
     ST_HIP(hipGetLastError());
     k_nn_out<<<(int)((M + 255) / 256), 256, 0, s>>>(M, metric, w.nn_key, idx_out, dist_out);
     ST_HIP(hipGetLastError());
@@ -2521,7 +2547,11 @@ int st_extend_batch(st_problem *p, int64_t B, const st_samples *s, const st_exte
     }
     if (B == 0) return ST_OK;
     int rc = extend_batch(p, B, *s, o, (hipStream_t)stream, false);
-    if (rc == ST_OK) p->iter++;
+    if (rc == ST_OK) {
+        p->iter++;
+        // (the bound counts prm.batch workers per iteration)
+        p->nodes_known += 2 * (B - p->prm.batch);
+    }
     return rc;
 }
 
@@ -2605,6 +2635,9 @@ int st_plan(st_problem *p, const st_budget *b, st_path *out) {
             rc = ST_EHIP;
             break;
         }
+        p->nodes_known = 0;
+        for (int i = 0; i < p->tree.n_pools; ++i) p->nodes_known += host->count[i];
+        p->nodes_iter = p->iter;
         if (host->first_iter >= 0 && out->first_solution_iter < 0) {
             out->first_solution_iter = host->first_iter;
             float t = 0.f;

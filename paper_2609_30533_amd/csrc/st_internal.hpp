@@ -214,6 +214,9 @@ struct st_problem {
     // a fresh problem's planner state and the start state, uploaded at creation
     st::PlanDev *d_plan0 = nullptr;
     float *d_start = nullptr;
+    // nodes when the host last wrote the trees or read their counts, and the
+    // iteration it did so at
+    int64_t nodes_known = 0, nodes_iter = 0;
     // what the planning calls keep (made by the first such call): pinned results,
     // a stream and the events of its clock.  The mutex covers the making and one
     // use of the results, so threads may read one handle's path together.
