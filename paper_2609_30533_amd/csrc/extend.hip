@@ -40,7 +40,6 @@ __device__ __forceinline__ unsigned long long pack_key(float dist_key, int32_t i
     return ((unsigned long long)__float_as_uint(dist_key) << 32) | (uint32_t)idx;
 }
 
-__device__ __forceinline__ int worker_pool(int8_t dir, int32_t grp) { return dir == 0 ? 0 : 1 + grp; }
 
 // ---------------------------------------------------------------------------
 // a1: sampling
@@ -1014,6 +1013,7 @@ __device__ __forceinline__ bool steer_worker(const SteerArgs &a, int64_t w, floa
     k.status[w] = status;
     k.new_idx[w] = -1;
     k.edge_valid[w] = ok ? 1 : 0;
+    k.ins_code[w] = ok ? (uint16_t)(1 + 2 * (dir == 0 ? 0 : 1 + g) + (idx < 0 ? 1 : 0)) : (uint16_t)0;
     k.parent[w] = ok ? idx : -1;
     if (!ok) return false;
 #pragma unroll
@@ -1080,15 +1080,32 @@ __global__ __launch_bounds__(64 * kFlatWaves) void k_steer_flat_multi(const Stee
 // ---------------------------------------------------------------------------
 
 
+// One chunk of kInsWorkers workers per thread: their codes and free flags in two
+// loads, a block-wide exclusive scan of (workers, nodes) to insert, and the chunk's
+// inserted workers as a dense list in LDS; then one worker per thread copies its
+// node, so that the copies of a pool's nodes (neighbours in the trees' rows) are
+// coalesced, with kInsFlight workers' loads in flight.  A block of a recycling
+// problem has 1/65 of the workers to insert but all of them to look at: bound by
+// the chain of dependent memory accesses (codes, payload, stores), not by bytes.
+// 8192 workers and 65 pools 7.9 us, 4096 workers and 9 pools 5.7 us; 31 and 10.6
+// with four workers per thread and pass, each copied by the thread that looked
+// at it behind five loads per worker.
+constexpr int kInsFlight = 4;
+constexpr int kInsShares = 4;  // blocks of the forward pool (one CU copies 2500 nodes in 9 us)
+
 template <bool MULTI>
 __global__ __launch_bounds__(1024) void k_insert(InsertArgs a0, const InsertArgs *__restrict__ av) {
-    __shared__ int wsum[32];
-    __shared__ int s_total, s_last;
-    __shared__ int s_bcnt[2], s_bbase[2];  // bridge bucket places of this pass
+    extern __shared__ float4 lds[];
+    uint32_t *s_list = reinterpret_cast<uint32_t *>(lds);  // worker of the chunk, virtual root (bit 15), node offset << 16
+    __shared__ uint32_t s_wave[16];
+    __shared__ int s_last, s_adv, s_base;
     const InsertArgs &a = MULTI ? av[blockIdx.y] : a0;
-    const int p = blockIdx.x;
+    // the forward pool has several blocks, each copying a share of the list
+    const int shares = MULTI || blockIdx.x >= kInsShares ? 1 : kInsShares;
+    const int share = shares > 1 ? (int)blockIdx.x : 0;
+    const int p = MULTI ? (int)blockIdx.x : max((int)blockIdx.x - (kInsShares - 1), 0);
     if (MULTI && p >= a.tree.n_pools) return;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = uniform(tid >> 6);
     const int nw = blockDim.x >> 6;
     PlanDev *pl = a.pl;
     const Work &k = a.w;
@@ -1097,101 +1114,116 @@ __global__ __launch_bounds__(1024) void k_insert(InsertArgs a0, const InsertArgs
     const int64_t snap = pl->count_snap[p];
     const int64_t avail = pool_cap(a.tree, p) - snap;
     int64_t running = 0;
-    if (tid == 0) s_last = 0;
-    if (tid < 2) s_bcnt[tid] = 0;
+    int last = 0;  // nodes inserted so far
     // the nearest-node buckets are consumed: empty for the next batch
-    if (p == 0)
+    if (p == 0 && share == 0)
         for (int i = tid; i < a.tree.n_pools; i += blockDim.x) k.bcnt[i] = 0;
-    // R consecutive workers per thread and pass; all their loads are issued
-    // before any store
-    constexpr int R = 4;
-    for (int64_t c0 = 0; c0 < a.B; c0 += (int64_t)blockDim.x * R) {
-        int need[R];
-        int32_t par0[R];
-        uint8_t ev[R], ef[R];
-        int8_t dr[R];
-        int32_t gr[R];
-        // unconditional loads (a worker past B reads worker B - 1 and is
-        // ignored): guarded loads would each wait before the next one issues
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t w = c0 + (int64_t)tid * R + r;
-            const bool in = w < a.B;
-            const int64_t wc = in ? w : a.B - 1;
-            const uint8_t v0 = k.edge_valid[wc], f0 = k.edge_free[wc];
-            const int8_t d0 = a.s.dir[wc];
-            const int32_t g0 = a.s.grp[wc], p0 = k.parent[wc];
-            ev[r] = in ? v0 : 0;
-            ef[r] = in ? f0 : 0;
-            dr[r] = in ? d0 : 0;
-            gr[r] = in ? g0 : 0;
-            par0[r] = in ? p0 : 0;
+    const int bset = p == 0 ? 0 : 1;  // bridge bucket of this pool's inserted workers
+    for (int64_t c0 = 0; c0 < a.B; c0 += (int64_t)blockDim.x * kInsWorkers) {
+        // code 1 + 2 pool + (the worker's tree is to be rooted first), 0 without an edge
+        const int64_t w0 = c0 + (int64_t)tid * kInsWorkers;
+        uint4 cd = make_uint4(0, 0, 0, 0);
+        uint2 fr = make_uint2(0, 0);
+        if (w0 < a.B) {  // (the arrays are padded to whole groups of kInsWorkers)
+            cd = *reinterpret_cast<const uint4 *>(k.ins_code + w0);
+            fr = *reinterpret_cast<const uint2 *>(k.edge_free + w0);
         }
-        int tot = 0;
-        bool trapped[R];
+        const uint32_t cw[4] = {cd.x, cd.y, cd.z, cd.w};
+        const uint32_t mine = 1u + 2u * (uint32_t)p;
+        uint32_t need = 0;  // two bits per worker: nodes to insert
+        uint32_t tot = 0;   // workers, and nodes << 16
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            need[r] = 0;
-            trapped[r] = false;
-            if (ev[r] && worker_pool(dr[r], gr[r]) == p) {
-                if (!ef[r]) trapped[r] = true;  // the extension collides
-                else need[r] = par0[r] < 0 ? 2 : 1;
+        for (int r = 0; r < kInsWorkers; ++r) {
+            const uint32_t code = (cw[r >> 1] >> (16 * (r & 1))) & 0xffffu;
+            const uint32_t f = ((r < 4 ? fr.x : fr.y) >> (8 * (r & 3))) & 0xffu;
+            const bool in = w0 + r < a.B && f != 0 && (code - mine) < 2u;
+            const uint32_t m = in ? 1u + (code - mine) : 0u;
+            need |= m << (2 * r);
+            tot += in ? 1u + (m << 16) : 0u;
+        }
+        const uint32_t incl = (uint32_t)wave_scan((int)tot, 0, [](int x, int y) { return x + y; });
+        if (lane == 63) s_wave[wv] = incl;
+        if (tid == 0) s_adv = 0;
+        __syncthreads();
+        // the waves' totals, scanned by every wave
+        const uint32_t wt = lane < nw ? s_wave[lane] : 0u;
+        const uint32_t ws = (uint32_t)wave_scan((int)wt, 0, [](int x, int y) { return x + y; });
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)ws, 63);
+        uint32_t off = incl - tot + (wv > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)ws, wv - 1) : 0u);
+#pragma unroll
+        for (int r = 0; r < kInsWorkers; ++r) {
+            const uint32_t m = (need >> (2 * r)) & 3u;
+            if (m) {
+                s_list[off & 0xffffu] =
+                    (uint32_t)(tid * kInsWorkers + r) | (m == 2u ? 0x8000u : 0u) | (off & 0xffff0000u);
+                off += 1u + (m << 16);
             }
-            tot += need[r];
         }
-        // the payload of this pool's new nodes, every load in flight together
-        // and ahead of the first store (a load behind a store waits for it)
-        // (no default values: a select on a guarded load would wait for it)
-        float xv[R][kMaxDof + 1], cn[R], rn[R], Tw[R];
+        const int cnt = (int)(total & 0xffffu), nodes = (int)(total >> 16);
+        // the inserted workers are the bridge queries (a6): one global atomic
+        // for this block's places in the bucket.  Offsets grow along the list, so
+        // what the pool has no room for is a tail of it; only then the length of
+        // the rest has to be found first.
+        const bool fits = running + nodes <= avail;
+        int adv = cnt;
+        auto reserve = [&]() {
+            const int n = adv * (share + 1) / shares - adv * share / shares;
+            if (tid == 0 && n > 0) s_base = atomicAdd(&k.bcnt[kBcntBridge + bset], n);
+        };
+        if (fits) reserve();
+        __syncthreads();
+        if (fits) {
+            last = (int)running + nodes;
+        } else {
+            for (int i = tid; i < cnt; i += blockDim.x) {
+                const uint32_t u = s_list[i];
+                const int64_t end = running + (u >> 16) + ((u & 0x8000u) ? 2 : 1);
+                const int64_t next =
+                    i + 1 < cnt ? running + (s_list[i + 1] >> 16) + ((s_list[i + 1] & 0x8000u) ? 2 : 1) : avail + 1;
+                if (end <= avail && next > avail) {
+                    s_adv = i + 1;
+                    s_last = (int)end;
+                }
+            }
+            __syncthreads();
+            adv = s_adv;
+            if (adv > 0) last = s_last;
+            reserve();
+            if (tid == 0) pl->overflow = 1;
+            __syncthreads();
+            if (share == 0)
+                for (int i = adv + tid; i < cnt; i += blockDim.x)
+                    k.status[c0 + (s_list[i] & 0x7fffu)] = ST_STATUS_DROPPED;
+        }
+        const int e0 = adv * share / shares, e1 = adv * (share + 1) / shares;  // this block's workers of the list
+        for (int i0 = e0 + tid; i0 < e1; i0 += kInsFlight * blockDim.x) {
+            // the payload of this thread's workers, every load in flight
+            // together and ahead of the first store (a load behind a store
+            // waits for it; one past the list repeats its last worker)
+            float xv[kInsFlight][kMaxDof + 1], cn[kInsFlight], rn[kInsFlight], Tw[kInsFlight];
+            int32_t par[kInsFlight];
+            uint32_t u[kInsFlight];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t w = c0 + (int64_t)tid * R + r;
-            if (need[r] > 0) {
+            for (int r = 0; r < kInsFlight; ++r) u[r] = s_list[min(i0 + r * (int)blockDim.x, e1 - 1)];
 #pragma unroll
-                for (int jj = 0; jj <= kMaxDof; ++jj)
-                    if (jj <= d) xv[r][jj] = k.xnew[w * W + jj];
+            for (int r = 0; r < kInsFlight; ++r) {
+                const int64_t w = c0 + (u[r] & 0x7fffu);
+#pragma unroll
+                for (int jj = 0; jj <= kMaxDof; ++jj) xv[r][jj] = k.xnew[w * W + min(jj, d)];
                 cn[r] = k.cost_new[w];
                 rn[r] = k.rootT_new[w];
                 Tw[r] = a.s.T[w];
+                par[r] = k.parent[w];
             }
-        }
-
-        // block-wide exclusive prefix of the threads' totals (worker order)
-        int incl = tot;
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += v;
-        }
-        if (lane == 63) wsum[wv] = incl;
-        __syncthreads();
-        if (tid == 0) {
-            int acc = 0;
-            for (int i = 0; i < nw; ++i) {
-                const int v = wsum[i];
-                wsum[i] = acc;
-                acc += v;
-            }
-            s_total = acc;
-        }
-        __syncthreads();
-        int64_t off = running + wsum[wv] + incl - tot;
-        int bset[R];  // bridge bucket of an inserted worker (0 forward, 1 backward)
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            bset[r] = -1;
-            if (need[r] == 0) continue;
-            const int64_t w = c0 + (int64_t)tid * R + r;
-            if (off + need[r] > avail) {
-                k.status[w] = ST_STATUS_DROPPED;
-                pl->overflow = 1;
-            } else {
-                int64_t idx = base + snap + off;
-                int32_t par = par0[r];
-                const bool virt = par < 0;
-                const float T = Tw[r];
-                if (virt) {
+            for (int r = 0; r < kInsFlight; ++r) {
+                const int i = i0 + r * (int)blockDim.x;
+                if (i >= e1) continue;
+                const int64_t w = c0 + (u[r] & 0x7fffu);
+                int64_t idx = base + snap + running + (u[r] >> 16);
+                if (u[r] & 0x8000u) {
                     // materialise the backward tree rooted at (q_g, T)
+                    const float T = Tw[r];
 #pragma unroll
                     for (int jj = 0; jj < kMaxDof; ++jj)
                         if (jj < d) a.tree.x[(int64_t)jj * a.tree.total + idx] = a.sc.q_g[jj];
@@ -1200,48 +1232,25 @@ __global__ __launch_bounds__(1024) void k_insert(InsertArgs a0, const InsertArgs
                     a.tree.cost[idx] = 0.f;
                     a.tree.rootT[idx] = T;
                     atomicMin((int *)&pl->minRootT[p - 1], __float_as_int(T));
-                    par = (int32_t)idx;
-                    k.parent[w] = par;
+                    par[r] = (int32_t)idx;
+                    k.parent[w] = par[r];
                     ++idx;
                 }
 #pragma unroll
                 for (int jj = 0; jj <= kMaxDof; ++jj)
                     if (jj <= d) a.tree.x[(int64_t)jj * a.tree.total + idx] = xv[r][jj];
-                a.tree.parent[idx] = par;
+                a.tree.parent[idx] = par[r];
                 a.tree.cost[idx] = cn[r];
                 a.tree.rootT[idx] = rn[r];
                 k.new_idx[w] = (int32_t)idx;
                 k.status[w] = ST_STATUS_ADVANCED;
-                atomicMax(&s_last, (int)(off + need[r]));
-                bset[r] = dr[r] == 0 ? 0 : 1;
+                k.border_br[(int64_t)bset * a.B + s_base + (i - e0)] = (int32_t)w;
             }
-            off += need[r];
         }
-        // the inserted workers are the bridge queries (a6): places within the
-        // block from LDS counters, then one global atomic per set and pass
-        int bpos[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) bpos[r] = wave_bucket_add(s_bcnt, bset[r]);
-        __syncthreads();
-        if (tid < 2) {
-            const int c = s_bcnt[tid];
-            s_bbase[tid] = c > 0 ? atomicAdd(&k.bcnt[kBcntBridge + tid], c) : 0;
-            s_bcnt[tid] = 0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (bset[r] >= 0)
-                k.border_br[(int64_t)bset[r] * a.B + s_bbase[bset[r]] + bpos[r]] = (int32_t)(c0 + (int64_t)tid * R + r);
-        // collided extensions (disjoint from the inserted workers), written
-        // last so that no load of this pass waits behind them
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (trapped[r]) k.status[c0 + (int64_t)tid * R + r] = ST_STATUS_TRAPPED;
-        running += s_total;
+        running += nodes;
         __syncthreads();
     }
-    if (tid == 0) pl->count[p] = (int32_t)(snap + s_last);
+    if (tid == 0 && share == 0) pl->count[p] = (int32_t)(snap + last);
 }
 
 // ---------------------------------------------------------------------------
@@ -1856,7 +1865,7 @@ static hipError_t dalloc(T **p, size_t n) {
 void work_free(st_problem *p) {
     Work &w = p->work;
     void *bufs[] = {w.dir, w.flags, w.grp, w.T, w.qr, w.tr, w.nn_key, w.tiles, w.n_tiles, w.bcnt, w.border_nn,
-                    w.border_br, w.xn, w.xnew, w.edge_valid, w.edge_free, w.first_hit, w.status, w.parent, w.new_idx, w.cost_new,
+                    w.border_br, w.xn, w.xnew, w.edge_valid, w.edge_free, w.ins_code, w.first_hit, w.status, w.parent, w.new_idx, w.cost_new,
                     w.rootT_new, w.br_key, w.br_idx, w.bridge, w.xb, w.br_valid, w.Up, w.Cp};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
@@ -1890,7 +1899,8 @@ int work_reserve(st_problem *p, int64_t B) {
     ST_HIP(dalloc(&w.xn, (size_t)B * W));
     ST_HIP(dalloc(&w.xnew, (size_t)B * W));
     ST_HIP(dalloc(&w.edge_valid, B));
-    ST_HIP(dalloc(&w.edge_free, B));
+    ST_HIP(dalloc(&w.edge_free, B + kInsWorkers));
+    ST_HIP(dalloc(&w.ins_code, B + kInsWorkers));
     ST_HIP(dalloc(&w.first_hit, B));
     ST_HIP(dalloc(&w.status, B));
     ST_HIP(dalloc(&w.parent, B));
@@ -2158,7 +2168,8 @@ int extend_batch(st_problem *p, int64_t B, const st_samples &in, const st_extend
         ST_HIP(launch_edge_args(a.edge_ext, s));
     }
     prof_mark(p, kStInsert, s);
-    k_insert<false><<<p->tree.n_pools, insert_threads(B), 0, s>>>(a.insert, nullptr);
+    k_insert<false><<<p->tree.n_pools + kInsShares - 1, insert_threads(B), insert_lds_bytes(insert_threads(B)), s>>>(
+        a.insert, nullptr);
     ST_HIP(hipGetLastError());
     prof_mark(p, kStBridgeSel, s);
     k_scan<kScanBridge, false, kTileQ, false>
@@ -2230,7 +2241,7 @@ int launch_batch_iteration(const BatchLaunch &L, hipStream_t s) {
             ST_HIP(launch_edge_items_multi(c.key, c.split_ext, L.edge_ext, c.members, c.n, c.nb_items_ext, c.lds, s));
         ST_HIP(launch_edge_finish_multi(L.edge_ext, L.P, L.nb_edge, s));
     }
-    k_insert<true><<<dim3(L.max_pools, L.P), L.ins_threads, 0, s>>>(InsertArgs{}, L.insert);
+    k_insert<true><<<dim3(L.max_pools, L.P), L.ins_threads, insert_lds_bytes(L.ins_threads), s>>>(InsertArgs{}, L.insert);
     scan_launch(IC<kScanBridge>{}, L.mt_br, L.P, L.all_members, L.scan_br);
     // the merge and the bridge edges' check, per scene class
     for (const BatchClass &c : L.classes) {

@@ -146,6 +146,7 @@ struct Work {
     int32_t *border_br;          // [2][Bcap]
     float *xn, *xnew;            // [B][d+1]
     uint8_t *edge_valid, *edge_free;
+    uint16_t *ins_code;          // 1 + 2 pool + (tree to be rooted first) of a worker with an edge, else 0
     int32_t *first_hit;          // [B] scratch for the edge checks
     int8_t *status;
     int32_t *parent, *new_idx;
@@ -256,19 +257,19 @@ inline int split_for(int setting, int64_t E) {
     if (setting >= 0) return setting;
     return E <= 256 ? 2 : 0;
 }
-// Threads of an insertion block (one block per pool, four workers per thread
-// and pass): whole waves, enough for one pass over B workers, at most 1024.
+// Threads of an insertion block (one block per pool): whole waves, enough to look
+// at B workers in one chunk, at most 1024; and its list of a chunk's workers.
+constexpr int kInsWorkers = 8;  // workers per thread and chunk
 inline int insert_threads(int64_t B) {
-    const int64_t t = ((B + 3) / 4 + 63) / 64 * 64;
+    const int64_t t = ((B + kInsWorkers - 1) / kInsWorkers + 63) / 64 * 64;
     return (int)(t < 64 ? 64 : (t > 1024 ? 1024 : t));
 }
+inline size_t insert_lds_bytes(int threads) { return (size_t)threads * kInsWorkers * sizeof(uint32_t); }
 // Record of one edge launch; the item kernel gets at least min_item_blocks blocks.
 EdgeArgs edge_args(const SceneDev &sc, const EdgeBufs &eb, int64_t E, const float *xa, const float *xb,
                    const uint8_t *valid, uint8_t *free_out, int32_t *first_hit, int lpe_shift,
                    unsigned long long *work, int min_item_blocks, int split_shift);
 hipError_t launch_edge_args(const EdgeArgs &a, hipStream_t s);
-// The item kernel alone, for edges whose records (state count, least hit)
-// and work items another kernel has written (the bridge check).
 // The same pipeline for P problems at once (records in device memory); the
 // item kernel runs once per scene class over its member records.
 hipError_t launch_edge_plan_multi(const EdgeArgs *d_args, int P, int max_nb_edge, hipStream_t s);
