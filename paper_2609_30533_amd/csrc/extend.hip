@@ -358,6 +358,15 @@ __global__ __launch_bounds__(1024) void k_prep(PrepArgs a) {
 
 enum { kScanRho = 0, kScanConfig = 1, kScanBridge = 2 };
 constexpr int kMinSliceNodes = 64;  // nearest-node scans: nodes per slice at least
+// Bridge scans: a tile's queries are few and their nodes are walked by few lanes
+// each, so slices are short (6-DOF arm at 4096 samples 83 us per iteration with
+// 16 or 32 nodes, 87 with 64, 95 with 128, 139 with 512).
+constexpr int kBridgeSliceNodes = 32;
+// Blocks of the bucketed scans at most (7-DOF arm at 8192 samples, five problems:
+// 134-298 us per iteration with 4096, 134-306 with 2048; a batch member: mixed
+// batch of 128, three batches: 224-258 us with 96 blocks, 222-260 with 64, 235-321
+// with 16).
+constexpr int kScanBlocks = 4096, kBridgeScanBlocks = 1024, kMemberScanBlocks = 96;
 
 
 // ---------------------------------------------------------------------------
@@ -580,38 +589,97 @@ __global__ __launch_bounds__(TQ) void k_scan(ScanArgs a0, const ScanArgs *__rest
     constexpr bool kFilter = FILTER && MODE != kScanBridge && TQ == kTileQ;
     __shared__ bf16x8 s_op[kFilter ? 3 : 1][kFilter ? TQ : 1];  // the filter's operand rows, eight places apart
     __shared__ int s_wide[4];
-    __shared__ int32_t s_pool[kMaxPools + 1], s_pre[kMaxPools + 1], s_cnt[kMaxPools + 1];
+    __shared__ int32_t s_pool[kMaxPools + 1], s_pre[kMaxPools + 1];
     __shared__ int32_t s_np;
+    __shared__ int s_hd[6];  // bucketed tiles: set (-1: no work), tile, slice, slices, queries, queries of set 0
     const ScanArgs &a = MULTI ? av[members[blockIdx.z]] : a0;
-    if (MULTI && (int)blockIdx.y >= a.nch) return;
-    const int t = blockIdx.x;
     const int tid = threadIdx.x;
     const PlanDev *pl = a.pl;
     const float U = a.use_snap ? pl->U_snap : pl->U;  // loaded ahead of the set-up barriers
+    // nodes of pool p that a scan of its own set, or of all backward pools, meets
+    auto pool_nodes = [&](int p, bool all) {
+        const int c = a.use_snap ? pl->count_snap[p] : pl->count[p];
+        return all && a.variant == ST_ROOT_RECYCLING && !pl->slot_active[p - 1] ? 0 : c;
+    };
+    auto filters = [&](int64_t queries, int64_t nodes) { return kFilter && queries * nodes >= kFilterMinPairs; };
+    // slices of a node set for one tile of queries: of kMinSliceNodes nodes at
+    // least (nearest node) or kBridgeSliceNodes (its merge reads one partial
+    // result per slice), of the filter kFilterSlice and no more than fill the chip
+    auto slices = [&](int64_t queries, int64_t nodes) {
+        const bool f = filters(queries, nodes);
+        const int at_least = f ? kFilterSlice : (MODE == kScanBridge ? kBridgeSliceNodes : kMinSliceNodes);
+        int64_t want = (nodes + at_least - 1) / at_least;
+        if (f) want = min<int64_t>(want, max<int64_t>(kFilterBlocks / ((queries + TQ - 1) / TQ), 1));
+        return (int)max<int64_t>(want, 1);
+    };
     int4 tile;             // set, first query, queries, sigma
     int64_t qrow = -1;     // bucket row of the tile's queries (-1: identity order)
     int64_t prow = -1;     // bridge buckets: the tile's first query in the two buckets' order
+    int slice = blockIdx.y, nch = a.nch, set_q = 0;
     if (a.bmode == 0) {
-        if (t >= a.n_tiles[0]) return;
-        tile = a.tiles[t];
+        if ((int)blockIdx.x >= a.n_tiles[0]) return;
+        tile = a.tiles[blockIdx.x];
+        set_q = TQ * a.n_tiles[0];
     } else {
-        // tile t is tile kt of bucket sb: the buckets' tiles in set order,
-        // from the counts (read together, then walked from LDS by every thread)
-        __shared__ int32_t s_bc[kMaxPools];
-        const int nsets = a.bmode == 1 ? a.tree.n_pools : 2;
-        // (a block of 64 threads may have fewer threads than sets)
-        for (int i = tid; i < nsets; i += TQ) s_bc[i] = a.bcnt[i];
-        __syncthreads();
-        int acc = 0, sb = 0, kt = -1;
-        for (; sb < nsets; ++sb) {
-            const int nt = (s_bc[sb] + TQ - 1) / TQ;
-            if (t < acc + nt) {
-                kt = t - acc;
-                break;
+        // The blocks are dealt out over the tiles and slices that the buckets'
+        // counts call for, sets in order, by the first wave (one set per lane).  In
+        // a grid of every possible tile and slice most blocks left at once, and
+        // starting them was most of the time of many scans: 83 us for 4096 queries
+        // and 3000 to 76000 nodes with 65 pools (48 now), three scans of a mixed
+        // batch of 128 113 us (42 now).
+        if (tid < 64) {
+            const int nsets = a.bmode == 1 ? a.tree.n_pools : 2;
+            const int b = blockIdx.x, grid = gridDim.x;
+            int all = 0;
+            if (a.bmode == 2) {
+                for (int p = 1 + tid; p < a.tree.n_pools; p += 64) all += pool_nodes(p, true);
+                all = wave_scan(all, 0, [](int x, int y) { return x + y; });
+                all = __builtin_amdgcn_readlane(all, 63);
             }
-            acc += nt;
+            int cap = a.nch, fs = -1, fk = 0, fc = 0, fn = 0, fq = 0;
+            for (int pass = 0; pass < 2; ++pass) {
+                int blocks = 0, tiles = 0;
+                fs = -1;
+                for (int s0 = 0; s0 < nsets; s0 += 64) {
+                    const int s = s0 + tid;
+                    const int q = s < nsets ? a.bcnt[s] : 0;
+                    const int nodes = s < nsets ? (a.bmode == 2 && s == 0 ? all : pool_nodes(a.bmode == 2 ? 0 : s, false)) : 0;
+                    const int nt = (q + TQ - 1) / TQ, want = min(slices(q, nodes), cap);
+                    const int nb = nt * want;
+                    const int incl = wave_scan(nb, 0, [](int x, int y) { return x + y; });
+                    const int at = b - (blocks + incl - nb);
+                    if (at >= 0 && at < nb) {
+                        fs = s;
+                        fk = at % nt;
+                        fc = at / nt;
+                        fn = want;
+                        fq = q;
+                    }
+                    blocks += __builtin_amdgcn_readlane(incl, 63);
+                    tiles += __builtin_amdgcn_readlane(wave_scan(nt, 0, [](int x, int y) { return x + y; }), 63);
+                }
+                // more than the grid holds: fewer slices (the grid has a block per tile at least)
+                if (blocks <= grid) break;
+                cap = max(grid / tiles, 1);
+            }
+            if (__ballot(fs >= 0) == 0) {
+                if (tid == 0) s_hd[0] = -1;
+            } else if (fs >= 0) {
+                s_hd[0] = fs;
+                s_hd[1] = fk;
+                s_hd[2] = fc;
+                s_hd[3] = fn;
+                s_hd[4] = fq;
+                s_hd[5] = a.bcnt[0];
+            }
         }
-        if (kt < 0) return;  // past the last tile (the same for the whole block)
+        __syncthreads();
+        const int sb = uniform(s_hd[0]);
+        if (sb < 0) return;  // the whole block
+        const int kt = uniform(s_hd[1]);
+        slice = uniform(s_hd[2]);
+        nch = uniform(s_hd[3]);
+        set_q = uniform(s_hd[4]);
         int set_id, sg;
         if (a.bmode == 1) {
             set_id = sb;
@@ -622,55 +690,49 @@ __global__ __launch_bounds__(TQ) void k_scan(ScanArgs a0, const ScanArgs *__rest
             // nodes into the backward forest, backward new nodes into the tree
             set_id = sb == 0 ? kSetAllBackward : 0;
             sg = sb == 0 ? -1 : 1;
+            if (kt == 0 && slice == 0 && tid == 0) a.nch_out[sb] = nch;
         }
-        tile = make_int4(set_id, kt * TQ, min(TQ, s_bc[sb] - kt * TQ), sg);
+        tile = make_int4(set_id, kt * TQ, min(TQ, set_q - kt * TQ), sg);
         qrow = (int64_t)sb * a.bstride;
-        if (a.bmode == 2) prow = (sb == 0 ? 0 : (int64_t)s_bc[0]) + (int64_t)kt * TQ;
+        if (a.bmode == 2) prow = (sb == 0 ? 0 : (int64_t)uniform(s_hd[5])) + (int64_t)kt * TQ;
     }
     const int set = tile.x, n = tile.z;
     const float sv = (float)tile.w * a.v;  // sigma * v
     const int d = a.tree.d;
-    // pools of the set and their prefix sums: the counts are loaded by one
-    // thread per pool, the prefix is formed from LDS
-    const int p_lo = set >= 0 ? set : 1, p_hi = set >= 0 ? set + 1 : a.tree.n_pools;
-    for (int p = p_lo + tid; p < p_hi; p += blockDim.x) {
-        int c = a.use_snap ? pl->count_snap[p] : pl->count[p];
-        if (a.variant == ST_ROOT_RECYCLING && set < 0 && !pl->slot_active[p - 1]) c = 0;
-        s_cnt[p - p_lo] = c;
-    }
-    __syncthreads();
-    if (tid == 0) {
+    // pools of the set and their prefix sums (one pool per lane of the first wave)
+    if (tid < 64) {
+        const int p_lo = set >= 0 ? set : 1, p_hi = set >= 0 ? set + 1 : a.tree.n_pools;
         int k = 0, acc = 0;
-        for (int p = p_lo; p < p_hi; ++p) {
-            const int c = s_cnt[p - p_lo];
-            if (c <= 0) continue;
-            s_pool[k] = p;
-            s_pre[k] = acc;
-            acc += c;
-            ++k;
+        for (int p0 = p_lo; p0 < p_hi; p0 += 64) {
+            const int p = p0 + tid;
+            const int c = p < p_hi ? pool_nodes(p, set < 0) : 0;
+            const uint64_t some = __ballot(c > 0);
+            const int incl = wave_scan(c, 0, [](int x, int y) { return x + y; });
+            if (c > 0) {
+                const int i = k + __popcll(some & ((1ull << tid) - 1ull));
+                s_pool[i] = p;
+                s_pre[i] = acc + incl - c;
+            }
+            k += __popcll(some);
+            acc += __builtin_amdgcn_readlane(incl, 63);
         }
-        s_pre[k] = acc;
-        s_np = k;
+        if (tid == 0) {
+            s_pre[k] = acc;
+            s_np = k;
+        }
     }
     __syncthreads();
     const int np = s_np;
     const int64_t total = s_pre[np];
-    // nearest-node scans of small node sets use fewer slices (each of at least
-    // kMinSliceNodes nodes); the blocks past them leave (the keys they would
-    // merge into start empty).  Bridge scans keep every slice: their merge
-    // reads one partial result per slice.
-    int nch = a.nch;
     // (the same for the whole block)
-    const int set_q = kFilter ? (a.bmode == 0 ? TQ * a.n_tiles[0] : a.bcnt[set]) : 0;
-    const bool filter = kFilter && n >= kFilterMinQueries && set_q * total >= kFilterMinPairs;
-    if (MODE != kScanBridge) {
-        const int slice = filter ? kFilterSlice : kMinSliceNodes;
-        int64_t want = (total + slice - 1) / slice;
-        if (filter) want = min<int64_t>(want, max(kFilterBlocks / ((set_q + TQ - 1) / TQ), 1));
-        nch = (int)min<int64_t>(nch, max<int64_t>(want, 1));
-        if ((int)blockIdx.y >= nch) return;
+    const bool filter = n >= kFilterMinQueries && filters(set_q, total);
+    if (a.bmode == 0) {
+        // the blocks past the slices of a small set leave (the keys they would
+        // merge into start empty)
+        nch = min(nch, slices(set_q, total));
+        if (slice >= nch) return;
     }
-    const int64_t c0 = (int64_t)blockIdx.y * total / nch, c1 = (int64_t)(blockIdx.y + 1) * total / nch;
+    const int64_t c0 = (int64_t)slice * total / nch, c1 = (int64_t)(slice + 1) * total / nch;
     const float *X = a.tree.x;
     const int64_t total_cap = a.tree.total;
     const float nanf_ = __int_as_float(0x7fc00000);
@@ -902,8 +964,8 @@ __global__ __launch_bounds__(TQ) void k_scan(ScanArgs a0, const ScanArgs *__rest
         // a bridge query's row: its place in the two buckets (the bridge
         // check's wave index, known there before the worker is), else the query
         const int64_t r = prow >= 0 ? prow + qs : q;
-        a.pkey[r * a.pstride + blockIdx.y] = pk;
-        a.pidx[r * a.pstride + blockIdx.y] = (int32_t)pi;
+        a.pkey[r * a.pstride + slice] = pk;
+        a.pidx[r * a.pstride + slice] = (int32_t)pi;
     } else {
         unsigned long long key = bi >= 0 ? pack_key(best, bi) : kNoKey;
         for (int o = 1; o < L; o <<= 1) {
@@ -1297,13 +1359,16 @@ __global__ __launch_bounds__(64 * kFlatWaves) void k_bridge_check(BridgeArgs a0,
     // the candidates of edge g: `sub` lanes each (a power of two), all groups
     // of lanes at once; the result goes to the LDS word of the edge
     uint32_t *s_best = reinterpret_cast<uint32_t *>(lds + sc.lds_f4 + flat_team_f4(G)) + 64 * waves;
-    const int sub = a.merge_lanes, per = 64 / sub, ls = lane & (sub - 1);
+    const int ny0 = uniform(k.bcnt[kBcntBridge + 4]), ny1 = uniform(k.bcnt[kBcntBridge + 5]);  // slices of the two scans
+    int sub = 1;
+    while (sub < 64 && sub < max(nb0 > 0 ? ny0 : 0, nb1 > 0 ? ny1 : 0)) sub *= 2;
+    const int per = 64 / sub, ls = lane & (sub - 1);
     for (int g0 = wv * per; g0 < cnt; g0 += waves * per) {
         const int g = g0 + lane / sub;
         unsigned long long bk = kNoKey;
         uint32_t bi = 0xffffffffu;
         if (g < cnt) {
-            for (int y = ls; y < a.nch; y += sub) {
+            for (int y = ls, ny = i0 + g < nb0 ? ny0 : ny1; y < ny; y += sub) {
                 const int64_t r = (int64_t)(i0 + g) * a.nch + y;
                 const int32_t ii = k.br_idx[r];
                 const unsigned long long kk = k.br_key[r];
@@ -1929,6 +1994,11 @@ static int nch_for(int tiles, int blocks = 1024) {
 }
 int nch_for_tiles(int tiles) { return nch_for(tiles); }
 
+// Blocks of a bucketed scan: at most `blocks`, one per tile at least.
+static int scan_grid(int tiles, int nch, int blocks) {
+    return std::max<int>(tiles, (int)std::min<int64_t>((int64_t)tiles * nch, blocks));
+}
+
 void prof_mark(st_problem *p, int stage, hipStream_t s) {
     if (!p->prof) return;
     if (p->prof_used == p->prof_ev.size()) {
@@ -2071,6 +2141,7 @@ void make_iter_args(const st_problem *p, int64_t B, const st_samples &in, const 
     sb.pidx = w.br_idx;
     sb.pstride = nch_br;  // query-major partials: [bridge query in bucket order][slice]
     sb.nch = nch_br;
+    sb.nch_out = w.bcnt + kBcntBridge + 4;
     BridgeArgs &ba = a.merge;
     ba.tree = p->tree;
     ba.B = B;
@@ -2078,8 +2149,6 @@ void make_iter_args(const st_problem *p, int64_t B, const st_samples &in, const 
     ba.dir = in.dir;
     ba.w = w;
     ba.sc = p->sc;
-    ba.merge_lanes = 1;
-    while (ba.merge_lanes < 64 && ba.merge_lanes < nch_br) ba.merge_lanes *= 2;
     ba.n = p->ebufs.n;
     ba.hit = p->ebufs.hit;
     ba.rest = p->ebufs.items;
@@ -2138,7 +2207,7 @@ int extend_batch(st_problem *p, int64_t B, const st_samples &in, const st_extend
     // node slices per scan tile: a budget of 4096 blocks for the nearest-node
     // scan, 1024 for the bridge scan (its per-slice candidates are merged by
     // the bridge check, which reads one per slice)
-    make_iter_args(p, B, in, out, nch_for(max_tiles(B, p->tree.n_pools), 4096), nch_for(max_tiles(B, 2), 1024), 1024,
+    make_iter_args(p, B, in, out, kMaxNch, nch_for(max_tiles(B, 2), 1024), 1024,
                    B, a);
     const int blocks = (int)((B + 255) / 256);
     prof_mark(p, kStNearest, s);
@@ -2147,7 +2216,7 @@ int extend_batch(st_problem *p, int64_t B, const st_samples &in, const st_extend
         ST_HIP(hipGetLastError());
     }
     launch_scan(p->prm.variant == ST_INTERVAL_ROOT ? ST_METRIC_RHO : ST_METRIC_CONFIG,
-                scan_may_filter(B, p->tree.total), dim3(a.mt_nn, a.scan_nn.nch), a.scan_nn, s);
+                scan_may_filter(B, p->tree.total), dim3(scan_grid(a.mt_nn, a.scan_nn.nch, kScanBlocks)), a.scan_nn, s);
     ST_HIP(hipGetLastError());
     if (a.edge_ext.flat) {
         // steering (a3) inside the extension check's launch (a4); the stage
@@ -2173,7 +2242,7 @@ int extend_batch(st_problem *p, int64_t B, const st_samples &in, const st_extend
     ST_HIP(hipGetLastError());
     prof_mark(p, kStBridgeSel, s);
     k_scan<kScanBridge, false, kTileQ, false>
-        <<<dim3(a.mt_br, a.scan_br.nch), kTileQ, 0, s>>>(a.scan_br, nullptr, nullptr);
+        <<<dim3(scan_grid(a.mt_br, a.scan_br.nch, kBridgeScanBlocks)), kTileQ, 0, s>>>(a.scan_br, nullptr, nullptr);
     ST_HIP(hipGetLastError());
     // the merge and the bridge edges' check in one launch (the stage timing
     // counts it as the bridge check)
@@ -2213,7 +2282,7 @@ int launch_batch_iteration(const BatchLaunch &L, hipStream_t s) {
     auto scan_multi = [&](auto mode, auto tq, auto filter, int mt, int n, const int32_t *members,
                           const ScanArgs *args) {
         k_scan<decltype(mode)::value, true, decltype(tq)::value, decltype(filter)::value>
-            <<<dim3(mt, L.nch, n), decltype(tq)::value, 0, s>>>(ScanArgs{}, args, members);
+            <<<dim3(scan_grid(mt, L.nch, kMemberScanBlocks), 1, n), decltype(tq)::value, 0, s>>>(ScanArgs{}, args, members);
     };
     auto scan_launch = [&](auto mode, int mt, int n, const int32_t *members, const ScanArgs *args) {
         constexpr bool near = decltype(mode)::value != kScanBridge;

@@ -56,7 +56,8 @@ struct ScanArgs {
     unsigned long long *pkey;  // bridges: [nch][pstride]
     int32_t *pidx;
     int64_t pstride;
-    int32_t nch;
+    int32_t nch;               // slices of a node set at most
+    int32_t *nch_out;          // bridges: slices of the two sets
 };
 
 struct SteerArgs {
@@ -85,7 +86,6 @@ struct BridgeArgs {
     TreeDev tree;
     int64_t B;
     int32_t nch;
-    int32_t merge_lanes;  // lanes that merge one worker's candidates (a power of two)
     int32_t blocks;       // blocks that share the advanced workers out (at least B / 64)
     int32_t w0;           // states per wave in the first phase
     const int8_t *dir;
