@@ -158,7 +158,6 @@ static int build_scene(st_problem *p, const st_problem_desc *D) {
     sc.v = (float)D->v_max;
     sc.H = (float)D->t_max;
     sc.h = (float)D->params.h;
-    sc.inv_h = (float)(1.0 / D->params.h);
     sc.v_d = (double)(float)D->v_max;
     sc.h_d = D->params.h;
     for (int j = 0; j < 8; ++j) {

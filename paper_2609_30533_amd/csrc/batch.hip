@@ -2,7 +2,7 @@
 //
 // Every kernel of one extend iteration is launched once for all member
 // problems, blockIdx.y (blockIdx.z for the scans) selecting the member's launch
-// record in device memory; the sampler and the edge item kernel, which are
+// record in device memory; the sampler and the edge checks, which are
 // specialised by robot kind, obstacle tile and obstacle-time mode, are launched
 // once per scene class over its members.  A small problem alone cannot fill
 // the 256 compute units; hundreds of them together do, and the whole
@@ -104,15 +104,15 @@ static int batch_build(st_batch *b) {
     BatchLaunch &L = b->L;
     L.P = P;
     if (P == 0) return ST_OK;
-    // node slices per scan tile: the tiles actually used are about one per
-    // 256 workers plus a partial one per node set, far fewer than the bound;
-    // aim at a few thousand scan blocks in total, at least 8 slices each so
-    // that a member's large tree is never scanned by a single block
+    // node slices per scan tile at most (the device uses what the sets need): a
+    // few thousand scan blocks in total over about a tile per 256 workers and a
+    // partial one per node set, at least 8 slices each so that a member's large
+    // tree is never scanned by a single block
     int64_t tiles = 0;
     for (st_problem *p : b->mem) tiles += (p->prm.batch + 255) / 256 + 2;
     const int nch = (int)std::min<int64_t>(64, std::max<int64_t>(8, 8192 / std::max<int64_t>(tiles, 1)));
-    // item blocks per member: about 16384 over the batch, at least four each,
-    // so that a member whose bridges are long spreads them over many waves
+    // item blocks per member of the chunked extension check (where a member is
+    // set to it): about 16384 over the batch, at least four each
     const int min_items = std::max(4, 16384 / P);
     int64_t all_edges = 0;
     for (st_problem *p : b->mem) all_edges += p->prm.batch;

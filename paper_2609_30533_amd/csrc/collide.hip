@@ -384,14 +384,6 @@ __global__ __launch_bounds__(256) void k_edge_finish_multi(const EdgeArgs *__res
     edge_finish_body(a, blockIdx.x);
 }
 
-// Obstacles held in registers per tile: 4, 8 or 16 (more obstacles run as
-// several tiles; 32 would cost occupancy for little gain).
-static int ot_for(int O_pad) {
-    if (O_pad <= 4) return 4;
-    if (O_pad <= 8) return 8;
-    return 16;
-}
-
 template <int V>
 using IC = std::integral_constant<int, V>;
 

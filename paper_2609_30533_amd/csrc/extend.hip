@@ -5,15 +5,18 @@
 //   sample   a1  Philox draws -> direction, group/slot, root time T, root check,
 //                q_r, t_r (Eq. 6), p_new rule
 //   prep         snapshot of pool counts and U; workers bucketed by node set
-//   scan     a2  nearest node: tiles of 64 queries (one per lane) stream a
-//                node set from HBM through LDS; packed (distance, index) keys
-//                are merged with 64-bit atomicMin, so ties go to the lowest index
+//   scan     a2  nearest node: tiles of 256 queries stream slices of a node set
+//                from HBM through LDS (large sets filtered on the matrix cores);
+//                packed (distance, index) keys are merged with 64-bit atomicMin,
+//                so ties go to the lowest index
 //   steer    a3  alpha = min(1, eta/rho) (interval root) or Eq. 8 (recycling)
-//   check    a4  edge checks (collide.hip), any-hit early exit
-//   insert   a5  one block per pool: prefix sum over workers in order, slots
-//                after the snapshot count, virtual roots materialised first
-//   bridge   a6  best-ranked candidate in the opposite set (arrival, rho, index),
-//                per-chunk partials merged per worker, then its edge check
+//   check    a4  extension edges, in the steering's launch (edge_flat.hpp)
+//   insert   a5  one block per pool (four for the forward one): prefix sum over
+//                workers in order, slots after the snapshot count, virtual roots
+//                materialised first
+//   bridge   a6  best-ranked candidate in the opposite set (arrival, rho, index):
+//                a scan with per-slice partials, their merge with the check of the
+//                edges, and the long edges' remaining states
 //   publish  a7  lexicographic minimum of (U', C', worker) against (U, C)
 //   roots    a8/a9 allocation update after a strict drop of U
 // Every worker sees the trees as they were when the batch started.
@@ -569,13 +572,12 @@ struct FilterQueries {
 };
 
 // One block = one tile of up to TQ queries (one per thread) against the
-// y-th of nch slices of its node set.  The set is a single pool or the
+// one of nch slices of its node set.  The set is a single pool or the
 // concatenation of the backward pools; nodes stream through LDS in rounds of
 // TQ (each thread loads one node, coalesced per SoA row), and the next round
 // is fetched into registers while the current one is scanned.  TQ is 256, or
 // 64 for a batch of problems with at most 64 samples each: their tiles hold a
-// few queries, and one-wave blocks keep four times as many of the launch's
-// (mostly empty) blocks in flight.  FILTER instances hold the matrix-core path
+// few queries, and four times as many one-wave blocks are in flight.  FILTER instances hold the matrix-core path
 // too and decide on the device; it takes 144 registers and 24 KB of LDS where
 // the plain scan has 52 and 12, so launches that cannot reach its number of pairs
 // take the plain instance (1852 queries of 13771 nodes 29 us in the one, 26 in the
@@ -1877,12 +1879,6 @@ __global__ void k_path_copy(TreeDev tree, const PlanDev *pl, int32_t nf, int32_t
 template <int V>
 using IC = std::integral_constant<int, V>;
 
-static int ot_for(int O_pad) {
-    if (O_pad <= 4) return 4;
-    if (O_pad <= 8) return 8;
-    return 16;
-}
-
 template <class F>
 static void dispatch_scene2(const SceneDev &sc, F &&f);
 
@@ -1938,7 +1934,6 @@ void work_free(st_problem *p) {
 }
 
 static int max_tiles(int64_t B, int n_sets) { return (int)((B + kTileQ - 1) / kTileQ) + n_sets; }
-int max_query_tiles(int64_t B, int n_sets) { return max_tiles(B, n_sets); }
 
 int work_reserve(st_problem *p, int64_t B) {
     if (p->work.Bcap >= B) return ST_OK;
@@ -1992,7 +1987,6 @@ static int nch_for(int tiles, int blocks = 1024) {
     int n = blocks / std::max(tiles, 1);
     return std::max(1, std::min(kMaxNch, n));
 }
-int nch_for_tiles(int tiles) { return nch_for(tiles); }
 
 // Blocks of a bucketed scan: at most `blocks`, one per tile at least.
 static int scan_grid(int tiles, int nch, int blocks) {
@@ -2204,11 +2198,10 @@ int extend_batch(st_problem *p, int64_t B, const st_samples &in, const st_extend
         if ((rc = edge_bufs_reserve(p->ebufs, B)) != ST_OK) return rc;
     }
     IterArgs a;
-    // node slices per scan tile: a budget of 4096 blocks for the nearest-node
-    // scan, 1024 for the bridge scan (its per-slice candidates are merged by
-    // the bridge check, which reads one per slice)
-    make_iter_args(p, B, in, out, kMaxNch, nch_for(max_tiles(B, 2), 1024), 1024,
-                   B, a);
+    // node slices per scan tile at most: the grid bounds the nearest-node scan's,
+    // a budget of 1024 blocks the bridge scan's (its per-slice candidates are
+    // merged by the bridge check, which reads one per slice)
+    make_iter_args(p, B, in, out, kMaxNch, nch_for(max_tiles(B, 2), 1024), 1024, B, a);
     const int blocks = (int)((B + 255) / 256);
     prof_mark(p, kStNearest, s);
     if (!bucketed) {

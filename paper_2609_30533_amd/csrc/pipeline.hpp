@@ -53,7 +53,7 @@ struct ScanArgs {
     const int32_t *bcnt, *border;
     int64_t bstride;
     unsigned long long *keys;  // nearest node: per-query atomic minimum
-    unsigned long long *pkey;  // bridges: [nch][pstride]
+    unsigned long long *pkey;  // bridges: [query in bucket order][pstride]
     int32_t *pidx;
     int64_t pstride;
     int32_t nch;               // slices of a node set at most
@@ -185,8 +185,6 @@ size_t scene_lds_bytes(const SceneDev &sc);
 // Dynamic LDS of the sampler: the scene, then (interval root) the guided
 // windows lo, hi, cum as doubles when they fit.
 size_t sample_lds_bytes(const st_problem *p, int32_t *nw_lds);
-int nch_for_tiles(int tiles);
 bool scan_may_filter(int64_t queries, int64_t nodes);
-int max_query_tiles(int64_t B, int n_sets);
 
 }  // namespace st

@@ -44,7 +44,7 @@ struct SceneDev {
     // q_g, boxes, constants (the segment table is at 0)
     int lds_sph, lds_t, lds_goal, lds_box, lds_const;
     int ot;                      // obstacles per register tile (4, 8 or 16; divides O_pad)
-    float v, H, h, inv_h;
+    float v, H, h;
     double v_d, h_d;
     float q_lo[8], q_hi[8], q_s[8], q_g[8];
     // static geometry (arms): boxes as 4 float4 rows: (axis_a, -axis_a . centre)

@@ -203,7 +203,7 @@ struct st_problem {
     bool use_graphs = true;
     // lanes per edge chunk (log2) for extension, bridge and st_check_edges launches
     int tune_ext = 5, tune_br = 4, tune_api = 5;
-    // lanes per state (log2) for the same three launches; -1 chooses by size
+    // lanes per state (log2) for extension and st_check_edges launches; -1 chooses by size
     int split_ext = -1, split_api = -1;
     // st_check_edges takes the chunked path when the caller chose its lanes
     bool api_lanes = false, api_split = false;
