@@ -115,7 +115,11 @@ static int batch_build(st_batch *b) {
     // set to it): about 16384 over the batch, at least four each
     const int min_items = std::max(4, 16384 / P);
     int64_t all_edges = 0;
-    for (st_problem *p : b->mem) all_edges += p->prm.batch;
+    int64_t kind_edges[2] = {0, 0};  // of the translating robots, of the arms
+    for (st_problem *p : b->mem) {
+        all_edges += p->prm.batch;
+        kind_edges[p->sc.kind != kTranslate] += p->prm.batch;
+    }
     std::vector<SampleArgs> smp(P);
     std::vector<ScanArgs> scan_nn(P), scan_br(P);
     std::vector<SteerArgs> steer(P);
@@ -142,11 +146,11 @@ static int batch_build(st_batch *b) {
         scan_nn[m] = a.scan_nn;
         scan_br[m] = a.scan_br;
         steer[m] = a.steer;
-        if (a.edge_ext.flat > 0) flat_shape_batch(a.edge_ext);
+        if (a.edge_ext.flat > 0) flat_shape_batch(a.edge_ext, kind_edges[p->sc.kind != kTranslate]);
         edge_ext[m] = a.edge_ext;
         ins[m] = a.insert;
         merge[m] = a.merge;
-        bridge_shape_batch(merge[m]);
+        bridge_shape_batch(merge[m], P);
         pub[m] = a.publish;
         roots[m] = a.roots;
         pls[m] = p->d_plan;

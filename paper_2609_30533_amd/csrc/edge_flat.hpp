@@ -271,11 +271,14 @@ inline void flat_shape_extension(EdgeArgs &a, int number) {
     flat_set(a, (int)std::max<int64_t>(1, std::min<int64_t>(4 * number, (a.E + 255) / 256)), 8, 8, 128);
 }
 
-// Extension edges of a batch member: 4 edges per block of four waves (the
-// mixed batch of 128 problems, three batches: 203 to 243 us per iteration; 223 to
-// 258 with 8 edges, 201 to 250 with 2; earlier, at 378 with 8 edges, 404 with 32
-// and eight waves, 438 with a wave per 8 edges).
-inline void flat_shape_batch(EdgeArgs &a) { flat_set(a, 4, 4, 4, 64); }
+// Extension edges of a batch member: blocks of four waves, with as many edges as
+// give the launch's `edges` (all members of the robot's kind) 768 blocks, three
+// per CU, within 4 to 16.  A mixed batch of 128 (2 k arm edges per iteration): 204-243
+// us per iteration; 203-243 with 4 throughout, 223-258 with 8, 234-264 with 16.  96 arms of 256 samples
+// (24 k): 311 us; 398 with 4, 363 with 8.
+inline void flat_shape_batch(EdgeArgs &a, int64_t edges) {
+    flat_set(a, (int)std::max<int64_t>(4, std::min<int64_t>(16, (edges + 767) / 768)), 4, 4, 64);
+}
 
 // The bridge check.  One problem: its advanced workers over 256 blocks of eight
 // waves (one block per CU: two do not fit the registers), first phases of 32
@@ -286,21 +289,23 @@ inline void flat_shape_batch(EdgeArgs &a) { flat_set(a, 4, 4, 4, 64); }
 // problems: 88 to 136 us per iteration; 99 to 140 with one wave and 64 states per
 // bridge and chunks of the rest, 86 to 133 (but 115 for 109) with 512 blocks and
 // no limit; 7-DOF arm at 8192: 182 to 343; 186 to 354; 196 to 351.  A batch
-// member: a block per four samples, at most 64 (243 us for the mixed batch, 248
-// without the bound, 268 with 16), no limit (its launch would be one more for
+// member: a block per four samples, at most 2048 in the launch within 16 to 64 per
+// member (243 us for the mixed batch with 64, 248 without a bound, 268 with 16; 96
+// arms of 256 samples 363 with 64, 333 with 16), no limit (its launch would be one more for
 // every scene class): mixed batch of 128 341 us with eight waves per block, 358
 // with four, 348 with a limit of 512, 390 with chunks (all with the scans of then).
 constexpr int kBridgeBlocks = 256, kBridgeW0 = 32, kBridgeLimit = 128, kBridgeSamplesBatch = 4,
-              kBridgeBlocksBatch = 64;
+              kBridgeBlocksBatch = 2048;
 inline void bridge_shape(BridgeArgs &a) {
     a.blocks = (int)std::max<int64_t>((a.B + kFlatMaxEdges - 1) / kFlatMaxEdges, std::min<int64_t>(kBridgeBlocks, a.B));
     a.w0 = kBridgeW0;
     a.limit = kBridgeLimit;
 }
-inline void bridge_shape_batch(BridgeArgs &a) {
+inline void bridge_shape_batch(BridgeArgs &a, int members) {
     const int64_t want = (a.B + kBridgeSamplesBatch - 1) / kBridgeSamplesBatch;
+    const int64_t most = std::max(16, std::min(64, kBridgeBlocksBatch / members));
     a.blocks = (int)std::max<int64_t>((a.B + kFlatMaxEdges - 1) / kFlatMaxEdges,
-                                      std::min<int64_t>(kBridgeBlocksBatch, want));
+                                      std::min<int64_t>(most, want));
     a.w0 = kBridgeW0;
     a.limit = INT32_MAX;
 }
