@@ -492,10 +492,10 @@ EdgeArgs edge_args(const SceneDev &sc, const EdgeBufs &eb, int64_t E, const floa
 }
 
 
-template <int KIND, int OT, int OBS>
+template <int KIND, int OT, int OBS, bool POOL>
 __global__ __launch_bounds__(64 * kFlatWaves) void k_edge_flat(EdgeArgs a) {
     extern __shared__ float4 lds[];
-    edge_flat_body<KIND, OT, OBS>(a, lds, blockIdx.x,
+    edge_flat_body<KIND, OT, OBS, POOL>(a, lds, blockIdx.x,
                                   [&](int64_t e, float (&A)[kMaxDof + 1], float (&B)[kMaxDof + 1]) {
                                       load_edge_rows(a.xa, a.xb, e, a.sc.d, A, B);
                                       return true;
@@ -509,8 +509,12 @@ hipError_t launch_check_edges_flat(const SceneDev &sc, int64_t E, const float *x
     flat_shape_api(a);
     const size_t lds = scene_lds_bytes(sc) + flat_lds_bytes(a);
     dispatch_scene(sc, [&](auto kind, auto ot, auto obs) {
-        k_edge_flat<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value>
-            <<<dim3((unsigned)flat_blocks(a)), dim3(64 * a.flat_waves), lds, s>>>(a);
+        if (E <= kFlatPoolEdges && a.flat_team == 1)
+            k_edge_flat<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value, true>
+                <<<dim3((unsigned)flat_blocks(a)), dim3(64 * a.flat_waves), lds, s>>>(a);
+        else
+            k_edge_flat<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value, false>
+                <<<dim3((unsigned)flat_blocks(a)), dim3(64 * a.flat_waves), lds, s>>>(a);
     });
     return hipGetLastError();
 }

@@ -213,21 +213,86 @@ __device__ __forceinline__ void edge_flat_team(const SceneDev &sc, float4 *lds, 
 }
 
 // A block's consecutive edges of an edge list: free / first hit, work counters.
-template <int KIND, int OT, int OBS, class Rows>
+// POOL: teams of one wave stop at state kFlatPoolLimit and the block's waves take
+// the long edges' remaining states together, 64 at a time in turn, each wave by
+// itself until a hit below its states is known.  One wave alone takes 231 us for
+// 8318 bridge-length edges of the arm with static geometry, pooled 173; the pooled
+// instance's 206 registers cost launches that fill the device (2^18 edges of the
+// 7-DOF arm 566 us, pooled 742), which keep the other.
+constexpr int kFlatPoolLimit = 64;
+constexpr int64_t kFlatPoolEdges = 10240;  // st_check_edges takes the pooled instance up to here
+// Arms between 1025 and this many edges: too few for a wave each to hide its
+// chain, too many for several; the chunked path spreads them better (1166
+// bridge-length edges of the 7-DOF arm 63 to 86 us here, 53 there).
+constexpr int64_t kFlatGapEdges = 2560;
+
+template <int KIND, int OT, int OBS, bool POOL, class Rows>
 __device__ __forceinline__ void edge_flat_body(const EdgeArgs &a, float4 *lds, int bx, Rows &&rows) {
+    __shared__ int2 s_left[POOL ? kFlatWaves * kFlatMaxEdges : 1];  // (team, edge of the team), first state left
+    __shared__ int s_cnt;
+    const SceneDev &sc = a.sc;
     const int G = a.flat, TW = a.flat_team;
-    const int wv = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int team = wv / TW, teams = (int)(blockDim.x >> 6) / TW;
+    const int wv = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63, nwv = blockDim.x >> 6;
+    const int team = wv / TW, teams = nwv / TW;
     const int64_t e = ((int64_t)bx * teams + team) * G + lane;
+    const bool pool = POOL && TW == 1 && nwv > 1;
+    if (POOL && threadIdx.x == 0) s_cnt = 0;  // (published by the staging's barrier)
     unsigned long long states = 0, edges = 0;
-    edge_flat_team<KIND, OT, OBS>(a.sc, lds, a.E, e, G, TW, a.flat_w0, INT32_MAX, rows,
-                                  [&](int64_t e, int32_t n, int32_t hit, int32_t) {
+    int32_t n_left = -1;
+    auto result = [&](int32_t n, int32_t hit) {
         const bool fr = hit == kNoHit;
         a.free_out[e] = fr ? 1 : 0;
         if (a.first_hit) a.first_hit[e] = fr ? -1 : hit;
         states = fr ? (unsigned long long)n + 1ull : (unsigned long long)hit + 1ull;
         edges = 1;
-    });
+    };
+    edge_flat_team<KIND, OT, OBS>(sc, lds, a.E, e, G, TW, a.flat_w0, pool ? kFlatPoolLimit : INT32_MAX, rows,
+                                  [&](int64_t, int32_t n, int32_t hit, int32_t lo) {
+                                      if (pool && hit == kNoHit && lo <= n) {
+                                          n_left = n;
+                                          s_left[atomicAdd(&s_cnt, 1)] = make_int2(team * kFlatMaxEdges + lane, lo);
+                                      } else {
+                                          result(n, hit);
+                                      }
+                                  });
+    if (pool) {
+        __syncthreads();
+        const int R = uniform(s_cnt);
+        auto edge_of = [&](int id, int32_t *&s_hit) {
+            float4 *row = lds + sc.lds_f4 + (id / kFlatMaxEdges) * flat_team_f4(G);
+            const int i = id % kFlatMaxEdges;
+            s_hit = reinterpret_cast<int32_t *>(row + 4 * G) + G + i;
+            return row + 4 * i;
+        };
+        for (int r = 0; r < R; ++r) {
+            const int2 it = s_left[r];
+            int32_t *s_hit;
+            const float4 *row = edge_of(uniform(it.x), s_hit);
+            const int n = uniform(s_hit[-G]);
+            const float4 a0 = row[0], a1 = row[1], b0 = row[2], b1 = row[3];
+            const float A[kMaxDof + 1] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+            const float B[kMaxDof + 1] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+            for (int base = uniform(it.y) + 64 * ((wv + r) % nwv); base <= n; base += 64 * nwv) {
+                if (uniform(__atomic_load_n(s_hit, __ATOMIC_RELAXED)) < base) break;
+                const int j = base + lane;
+                float q[kMaxDof];
+                float t;
+                edge_state(A, B, min(j, n), n, q, t);
+                const bool hit = state_hits<KIND, OT, OBS, true>(sc, lds, q, t, j <= n, ~0ull, (1ull << lane) - 1ull);
+                const uint64_t hm = __ballot(hit && j <= n);
+                if (hm) {
+                    if (lane == 0) atomicMin(s_hit, base + (int)__builtin_ctzll(hm));
+                    break;
+                }
+            }
+        }
+        __syncthreads();
+        if (n_left >= 0) {
+            int32_t *s_hit;
+            (void)edge_of(team * kFlatMaxEdges + lane, s_hit);
+            result(n_left, *s_hit);
+        }
+    }
     if (a.work && wv == team * TW) {
         for (int o = 32; o > 0; o >>= 1) {
             states += __shfl_down(states, o, 64);

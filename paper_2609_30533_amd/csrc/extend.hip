@@ -1108,7 +1108,7 @@ __global__ __launch_bounds__(256) void k_steer(SteerArgs a0, const SteerArgs *__
 // the resulting edges (a4), with no round trip through a separate launch.
 template <int KIND, int OT, int OBS>
 __device__ __forceinline__ void steer_flat_body(const SteerArgs &sa, const EdgeArgs &ea, float4 *lds, int bx) {
-    edge_flat_body<KIND, OT, OBS>(ea, lds, bx, [&](int64_t e, float (&A)[kMaxDof + 1], float (&B)[kMaxDof + 1]) {
+    edge_flat_body<KIND, OT, OBS, false>(ea, lds, bx, [&](int64_t e, float (&A)[kMaxDof + 1], float (&B)[kMaxDof + 1]) {
         float xn[kMaxDof + 1], xnew[kMaxDof + 1];
         if (!steer_worker(sa, e, xn, xnew)) return false;
         // both endpoints, earlier time first
