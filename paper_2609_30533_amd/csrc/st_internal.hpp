@@ -93,8 +93,12 @@ struct WindowsDev {
 // Edge-check pipeline: hit[e] holds kNoHit until a colliding state is found;
 // the rank counters sit kCntStride ints (128 bytes) apart.
 constexpr int32_t kNoHit = 0x7fffffff;
-constexpr int kBcntBridge = 128;  // bridge bucket counters (own cache lines)
-constexpr int kBcntSize = 160;
+// Bucket counters: one per nearest-node set (pool), then on a cache line of their
+// own the bridge buckets' [0], [1], the long bridges' [2] and the slices of the
+// two bridge scans [4], [5].
+constexpr int kBcntBridge = (kMaxPools + 31) / 32 * 32;
+constexpr int kBcntSize = kBcntBridge + 32;
+static_assert(kBcntBridge >= kMaxPools, "a pool's counter must not be a bridge bucket's");
 constexpr int kCntStride = 32;
 
 // Work buffers of the edge-check pipeline (capacity cap edges).
