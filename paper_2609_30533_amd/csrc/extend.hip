@@ -419,7 +419,7 @@ constexpr int64_t kFilterMinPairs = 1ll << 27;
 constexpr float kFilterEps = 1.0f / 16384.0f;   // 2^-14
 constexpr float kFilterSlack = 1.0f / 131072.0f; // 2^-17
 constexpr float kFilterMax = 1e30f;
-constexpr float kFilterPass = -1.7014118e38f;    // -2^127: passes whatever is added
+constexpr float kFilterPass = -1.7014118e38f;    // -2^127: a node that passes (its w2 is no larger than a bound below kFilterMax)
 
 // x in three bf16 parts (24 bits).
 __device__ __forceinline__ void split3(float x, __bf16 &h, __bf16 &m, __bf16 &l) {
@@ -467,22 +467,26 @@ struct FilterQueries {
 
     // places 24 .. 26 (lanes 32 ..): the constant for the present bound
     __device__ __forceinline__ void set_bound(float wide, float &h) {
+        // Everything passes while there is no bound to compare with (rho: the cone
+        // alone, as w2 <= wide for every node of the round) and for queries and
+        // bounds out of range: minus infinity, which no w2 that is finite outweighs.
         float c;
+        bool pass;
         if (MODE == kScanConfig) {
-            // no bound yet: everything passes
-            c = thr < INFINITY ? q2 - (thr * (1.0f + kFilterSlack) + 1e-30f) : kFilterPass;
+            c = q2 - (thr * (1.0f + kFilterSlack) + 1e-30f);
+            pass = !(q2 < kFilterMax) || !(thr < kFilterMax);
             h = 0.f;
         } else {
-            // no bound yet: the cone alone (w2 <= wide for every node of the round)
             h = thr < INFINITY ? 0.5f * thr : wide;
             c = q2 - (h + (h * kFilterSlack + 1e-30f));
+            pass = !(q2 < kFilterMax) || !(h < kFilterMax);
         }
-        if (!(q2 < kFilterMax) || !(h < kFilterMax)) c = kFilterPass, h = 0.f;
-        if (!act) c = kFilterMax;
+        if (pass) c = 0.f, h = 0.f;
+        if (!act) c = kFilterMax, pass = false;
         if (threadIdx.x & 32) {
             __bf16 u, v, w;
             split3(c, u, v, w);
-            b1[0] = u;
+            b1[0] = pass ? (__bf16)(-INFINITY) : u;
             b1[1] = v;
             b1[2] = w;
         }
