@@ -590,7 +590,7 @@ template <int MODE, bool MULTI, int TQ, bool FILTER>
 __global__ __launch_bounds__(TQ) void k_scan(ScanArgs a0, const ScanArgs *__restrict__ av,
                                              const int32_t *__restrict__ members) {
     __shared__ __align__(16) float sx[TQ][8];
-    __shared__ float sT[TQ];
+    __shared__ __align__(16) float sT[TQ];  // (the filter reads four at a time)
     __shared__ int32_t sI[TQ];
     constexpr bool kFilter = FILTER && MODE != kScanBridge && TQ == kTileQ;
     __shared__ bf16x8 s_op[kFilter ? 3 : 1][kFilter ? TQ : 1];  // the filter's operand rows, eight places apart
