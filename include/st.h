@@ -452,9 +452,9 @@ int st_proposal_set(st_problem *p, const float *z, float mix, void *stream);
  * tile (4, 8 or 16, dividing the padded obstacle count; 0 keeps the current
  * value) and lanes per edge chunk for extension edges, bridge edges and
  * st_check_edges (powers of two up to 64; 0 keeps; choosing lanes for
- * st_check_edges puts it on the chunked path, which it takes by itself for arms
- * and 1025 to 2560 edges;
- * the lanes of bridge edges are kept and reported, but their check lays states
+ * st_check_edges puts it on the chunked path, which keeps work buffers in the
+ * handle: its calls on one handle must not overlap, and one that is captured
+ * needs an earlier call of its size; the lanes of bridge edges are kept and reported, but their check lays states
  * end to end and has no chunks).  Results do not depend on these.
  * Synchronous; drops captured iteration graphs. */
 int st_set_tuning(st_problem *p, int32_t obstacle_tile, int32_t lanes_extension, int32_t lanes_bridge,

@@ -9,7 +9,6 @@
 #include <chrono>
 #include <numeric>
 
-#include "edge_flat.hpp"
 #include "pipeline.hpp"
 #include "st_internal.hpp"
 
@@ -675,10 +674,8 @@ int st_check_edges(st_problem *p, int64_t E, const float *xa, const float *xb, u
                    int32_t *first_hit, void *stream) {
     if (!p || E < 0 || (E > 0 && (!xa || !xb || !free_out))) return fail(ST_EINVAL, "st_check_edges: bad arguments");
     if (E == 0) return ST_OK;
-    // the one-kernel check, unless the caller chose lanes for the chunked one or
-    // that is the faster one (arms, some number of edges; see kFlatGapEdges)
-    const bool gap = p->sc.kind != kTranslate && E > 1024 && E <= kFlatGapEdges;
-    if (!p->api_lanes && !p->api_split && !gap) {
+    // the one-kernel check, unless the caller chose lanes for the chunked one
+    if (!p->api_lanes && !p->api_split) {
         ST_HIP(launch_check_edges_flat(p->sc, E, xa, xb, free_out, first_hit, (hipStream_t)stream));
         return ST_OK;
     }

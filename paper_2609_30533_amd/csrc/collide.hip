@@ -493,7 +493,7 @@ EdgeArgs edge_args(const SceneDev &sc, const EdgeBufs &eb, int64_t E, const floa
 
 
 template <int KIND, int OT, int OBS, bool POOL>
-__global__ __launch_bounds__(64 * kFlatWaves) void k_edge_flat(EdgeArgs a) {
+__global__ __launch_bounds__(64 * kFlatApiWaves) void k_edge_flat(EdgeArgs a) {
     extern __shared__ float4 lds[];
     edge_flat_body<KIND, OT, OBS, POOL>(a, lds, blockIdx.x,
                                   [&](int64_t e, float (&A)[kMaxDof + 1], float (&B)[kMaxDof + 1]) {
@@ -509,7 +509,7 @@ hipError_t launch_check_edges_flat(const SceneDev &sc, int64_t E, const float *x
     flat_shape_api(a);
     const size_t lds = scene_lds_bytes(sc) + flat_lds_bytes(a);
     dispatch_scene(sc, [&](auto kind, auto ot, auto obs) {
-        if (E <= kFlatPoolEdges && a.flat_team == 1)
+        if (a.flat_team == 1)
             k_edge_flat<decltype(kind)::value, decltype(ot)::value, decltype(obs)::value, true>
                 <<<dim3((unsigned)flat_blocks(a)), dim3(64 * a.flat_waves), lds, s>>>(a);
         else

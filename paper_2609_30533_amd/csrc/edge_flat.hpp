@@ -69,13 +69,15 @@ __device__ __forceinline__ void edge_state(const float (&A)[kMaxDof + 1], const 
 
 // ---------------------------------------------------------------------------
 // Edge check in one kernel.  A team of waves takes G consecutive edges (G <=
-// 64) and decides them completely (state counts, checks, free / first hit,
-// work counters), in phases.  A phase checks the states [lo, lo + width) of
-// every edge of the team still without a hit, laid end to end and dealt to the
-// team's waves in rounds; the next phase starts behind them, wider.  A team is
-// one wave (no barrier after the scene is staged, and no wave waits for
-// another), or the whole block when a launch has fewer edges than the device
-// has SIMDs.
+// 64) and decides them (state counts, checks, free / first hit, work counters)
+// in phases.  A phase checks the states [lo, lo + width) of every edge of the
+// team still without a hit, laid end to end and dealt to the team's waves in
+// rounds; the next phase starts behind them, wider.  A team is the whole block,
+// or, in launches with many edges for every wave of the device, one wave for
+// the first phase (no barriers) and then, for what that leaves, the whole block:
+// a wave by itself held up to eight times its share where the long free edges
+// lie unevenly (3000 extension edges of the 7-DOF arm 59 us, 37 for the chunked
+// kernels, 35 so; 65536 of them 270 and 192).
 //
 // Bound by VALU issue (a state check of the 6-DOF arm is about 3700
 // instructions, 2700 of them sphere pairs) and, with a round or two per wave,
@@ -96,13 +98,17 @@ __device__ __forceinline__ void edge_state(const float (&A)[kMaxDof + 1], const 
 constexpr int kFlatMaxEdges = 64;  // edges per team at most (one per lane)
 constexpr int kFlatMaxShift = 3;   // lanes per state at most (log2)
 constexpr int kFlatMaxWidth = 4096;// states of one edge per phase at most
-constexpr int kFlatWaves = 8;      // waves per block at most
+constexpr int kFlatWaves = 8;      // waves of a block with the planner's own edges at most
+constexpr int kFlatApiWaves = 12;  // and of one of st_check_edges (three per SIMD, what 168 registers leave room for)
 
-// Dynamic LDS behind the scene: per team both endpoint rows, state counts and
-// least hits, per wave the edges that start in its round.
-inline __host__ __device__ int flat_team_f4(int G) { return 4 * G + (2 * G + 3) / 4; }
-inline size_t flat_lds_bytes(int waves, int team, int G) {
-    return (size_t)(waves / team) * flat_team_f4(G) * 16 + (size_t)waves * 64 * sizeof(int32_t);
+// Dynamic LDS behind the scene: of the block's edges both endpoint rows, state
+// counts, least hits and, when the block pools its long edges, the first state
+// left and the list of them; per wave the edges that start in its round.
+inline __host__ __device__ int flat_words(int edges, int waves, bool pool) {
+    return edges * (pool ? 20 : 18) + 64 * waves;
+}
+inline size_t flat_lds_bytes(int waves, int team, int G, bool pool = false) {
+    return (size_t)flat_words(waves / team * G, waves, pool) * sizeof(int32_t);
 }
 
 // Inclusive scan over the wave's lanes in six cross-lane steps (row shifts,
@@ -125,60 +131,88 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// One team's edges: the lane's edge e (lane < G; none from E on), G edges for
-// TW waves of the block, at most w0 states of an edge in the first phase, no
-// phase that starts at state `limit` or above.
+// A block's edges, G for every TW waves: the lane's edge e (lane < G; none from E
+// on), at most w0 states of an edge in the first phase, no phase that starts at
+// state `limit` or above.  POOL (teams of one wave): what the teams leave at the
+// limit is checked by the whole block as one team, 64 edges at a time.
 // rows(e, A, B) fills both endpoints, earlier time first, and returns false for
-// an edge not to check; done(e, n, hit, lo) gets, on the lanes of the team's
-// first wave that have an edge that was checked, its state count, its least hit
-// and the first state that was left to the caller (above n without a limit).
-template <int KIND, int OT, int OBS, class Rows, class Done>
+// an edge not to check; done(e, n, hit, lo) gets, on the lanes of a team's first
+// wave that have an edge that was checked, its state count, its least hit and the
+// first state that was left to the caller (above n without a limit or pooled).
+template <int KIND, int OT, int OBS, bool POOL, class Rows, class Done>
 __device__ __forceinline__ void edge_flat_team(const SceneDev &sc, float4 *lds, int64_t E, int64_t e, int G, int TW,
                                                int w0, int limit, Rows &&rows, Done &&done) {
+    __shared__ int s_cnt;
     const int d = sc.d;
     const int wv = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63, nwv = blockDim.x >> 6;
-    const int team = wv / TW, tw = wv - team * TW, teams = nwv / TW;
-    float4 *s_row = lds + sc.lds_f4 + team * flat_team_f4(G);  // edge i: A at [4 i], B at [4 i + 2]
-    int32_t *s_n = reinterpret_cast<int32_t *>(s_row + 4 * G), *s_hit = s_n + G;
-    int32_t *s_map = reinterpret_cast<int32_t *>(lds + sc.lds_f4 + teams * flat_team_f4(G)) + 64 * wv;
+    const int team = wv / TW, NB = nwv / TW * G;
+    float4 *s_row = lds + sc.lds_f4;  // edge i of the block: A at [4 i], B at [4 i + 2]
+    int32_t *s_n = reinterpret_cast<int32_t *>(s_row + 4 * NB), *s_hit = s_n + NB;
+    int32_t *s_lo = s_hit + NB, *s_list = s_lo + NB;  // (pooled blocks)
+    int32_t *s_map = s_n + (POOL ? 4 : 2) * NB + 64 * wv;
+    // waves of the lane's team, the wave's place in it, the lane's edge of the block
+    int W = TW, tw = wv - team * TW, id = team * G + lane;
+    bool has = lane < G;
     // the edges' rows first, so that the producer's loads are in flight while
     // other threads stage the scene; the staging's barrier also publishes the
     // rows
-    int32_t n_own = -1;
-    if (tw == 0 && lane < G) {
+    if (tw == 0 && has) {
+        int32_t n = -1;
         if (e < E) {
             float A[kMaxDof + 1], B[kMaxDof + 1];
             if (rows(e, A, B)) {
-                n_own = edge_states(A, B, d, sc.v_d, sc.h_d);
-                s_row[4 * lane] = make_float4(A[0], A[1], A[2], A[3]);
-                s_row[4 * lane + 1] = make_float4(A[4], A[5], A[6], A[7]);
-                s_row[4 * lane + 2] = make_float4(B[0], B[1], B[2], B[3]);
-                s_row[4 * lane + 3] = make_float4(B[4], B[5], B[6], B[7]);
+                n = edge_states(A, B, d, sc.v_d, sc.h_d);
+                s_row[4 * id] = make_float4(A[0], A[1], A[2], A[3]);
+                s_row[4 * id + 1] = make_float4(A[4], A[5], A[6], A[7]);
+                s_row[4 * id + 2] = make_float4(B[0], B[1], B[2], B[3]);
+                s_row[4 * id + 3] = make_float4(B[4], B[5], B[6], B[7]);
             }
         }
-        s_n[lane] = n_own;
-        s_hit[lane] = kNoHit;
+        s_n[id] = n;
+        s_hit[id] = kNoHit;
     }
+    if (POOL && threadIdx.x == 0) s_cnt = 0;
     stage_obstacles(sc, lds);
-    if (tw != 0 && lane < G) n_own = s_n[lane];
-    int lo = 0, width = w0;
-    int32_t hit_own;
+    int32_t n_own = has ? s_n[id] : -1, lo = 0;  // (an edge not to check has n = -1)
+    int width = w0, pooled = 0;
     for (;;) {
         // the phase's states of the lane's edge and their place
-        hit_own = lane < G ? __atomic_load_n(&s_hit[lane], __ATOMIC_RELAXED) : 0;
-        const int left = n_own - lo + 1;  // (an edge not to check has n = -1)
-        const int c = lane < G && hit_own == kNoHit && left > 0 && lo < limit ? min(left, width) : 0;
+        const int left = n_own - lo + 1;
+        int c = 0;
+        if (has && left > 0 && lo < limit && __atomic_load_n(&s_hit[id], __ATOMIC_RELAXED) == kNoHit) c = min(left, width);
         const int incl = wave_scan(c, 0, [](int x, int y) { return x + y; });
         const int off = incl - c, T = __builtin_amdgcn_readlane(incl, 63);
         const int m = __popcll(__ballot(c > 0));
-        if (TW > 1) __syncthreads();  // no wave merges a hit before all have read them
-        if (T == 0) break;
+        if (W > 1) __syncthreads();  // no wave merges a hit before all have read them
+        if (T == 0) {
+            if (!POOL) break;
+            if (pooled == 0) {
+                // the teams' long edges become the block's
+                if (has && left > 0 && s_hit[id] == kNoHit) {
+                    s_lo[id] = lo;
+                    s_list[atomicAdd(&s_cnt, 1)] = id;
+                }
+                __syncthreads();
+                W = nwv;
+                tw = wv;
+                limit = INT32_MAX;
+            }
+            const int R = uniform(s_cnt);
+            if (pooled >= R) break;
+            has = pooled + lane < R;
+            id = has ? s_list[pooled + lane] : 0;
+            n_own = has ? s_n[id] : -1;
+            lo = has ? s_lo[id] : 0;
+            width = max(64, 64 * W / min(64, R - pooled));
+            pooled += 64;
+            continue;
+        }
         // lanes per state: what the phase's states leave free
         int shift = 0;
         if (KIND != kTranslate)
-            while (shift < kFlatMaxShift && (T << (shift + 1)) <= 64 * TW) ++shift;
+            while (shift < kFlatMaxShift && (T << (shift + 1)) <= 64 * W) ++shift;
         const int per = 64 >> shift, part = lane & ((1 << shift) - 1);
-        for (int base = tw * per; base < T; base += per * TW) {
+        for (int base = tw * per; base < T; base += per * W) {
             // the edge of each state of the round: edges mark the slot they
             // start in, a scan carries the mark on
             s_map[lane] = -1;
@@ -186,10 +220,10 @@ __device__ __forceinline__ void edge_flat_team(const SceneDev &sc, float4 *lds, 
             if (c > 0 && off < base + per && off + c > base) s_map[max(off - base, 0)] = lane;
             wave_lds_fence();
             const int mark = wave_scan(s_map[lane], -1, [](int x, int y) { return max(x, y); });
-            const int i = __shfl(mark, lane >> shift, 64);
-            const int o0 = __shfl(off, i, 64);
-            const int32_t n = __shfl(n_own, i, 64);
-            const int g = base + (lane >> shift), j = lo + g - o0;
+            const int k = __shfl(mark, lane >> shift, 64);
+            const int o0 = __shfl(off, k, 64), i = __shfl(id, k, 64);
+            const int32_t n = __shfl(n_own, k, 64);
+            const int g = base + (lane >> shift), j = __shfl(lo, k, 64) + g - o0;
             // a state above a known hit of its edge is not needed
             const bool act = g < T && j <= __atomic_load_n(&s_hit[i], __ATOMIC_RELAXED);
             // the lanes of lower states of this edge in this round (FIRST rule)
@@ -204,95 +238,38 @@ __device__ __forceinline__ void edge_flat_team(const SceneDev &sc, float4 *lds, 
                 sc, lds, q, t, act, 0ull, lower, part, shift);
             if (hit && act && part == 0) atomicMin(&s_hit[i], j);
         }
-        if (TW > 1) __syncthreads();
+        if (W > 1) __syncthreads();
         lo += width;
         // at least four times as wide, and half a state per lane
-        width = min(kFlatMaxWidth, max(4 * width, 32 * TW / m));
+        width = min(kFlatMaxWidth, max(4 * width, 32 * W / m));
     }
-    if (tw == 0 && lane < G && n_own >= 0) done(e, n_own, hit_own, lo);
+    if (POOL) {
+        __syncthreads();
+        has = lane < G;
+        id = team * G + lane;
+        n_own = has ? s_n[id] : -1;
+        lo = INT32_MAX;
+    }
+    if (wv == team * TW && has && n_own >= 0) done(e, n_own, s_hit[id], lo);
 }
 
 // A block's consecutive edges of an edge list: free / first hit, work counters.
-// POOL: teams of one wave stop at state kFlatPoolLimit and the block's waves take
-// the long edges' remaining states together, 64 at a time in turn, each wave by
-// itself until a hit below its states is known.  One wave alone takes 231 us for
-// 8318 bridge-length edges of the arm with static geometry, pooled 173; the pooled
-// instance's 206 registers cost launches that fill the device (2^18 edges of the
-// 7-DOF arm 566 us, pooled 742), which keep the other.
-constexpr int kFlatPoolLimit = 64;
-constexpr int64_t kFlatPoolEdges = 10240;  // st_check_edges takes the pooled instance up to here
-// Arms between 1025 and this many edges: too few for a wave each to hide its
-// chain, too many for several; the chunked path spreads them better (1166
-// bridge-length edges of the 7-DOF arm 63 to 86 us here, 53 there).
-constexpr int64_t kFlatGapEdges = 2560;
-
+// POOL: teams of one wave for the first phase only.
 template <int KIND, int OT, int OBS, bool POOL, class Rows>
 __device__ __forceinline__ void edge_flat_body(const EdgeArgs &a, float4 *lds, int bx, Rows &&rows) {
-    __shared__ int2 s_left[POOL ? kFlatWaves * kFlatMaxEdges : 1];  // (team, edge of the team), first state left
-    __shared__ int s_cnt;
-    const SceneDev &sc = a.sc;
     const int G = a.flat, TW = a.flat_team;
     const int wv = uniform(threadIdx.x >> 6), lane = threadIdx.x & 63, nwv = blockDim.x >> 6;
     const int team = wv / TW, teams = nwv / TW;
     const int64_t e = ((int64_t)bx * teams + team) * G + lane;
-    const bool pool = POOL && TW == 1 && nwv > 1;
-    if (POOL && threadIdx.x == 0) s_cnt = 0;  // (published by the staging's barrier)
     unsigned long long states = 0, edges = 0;
-    int32_t n_left = -1;
-    auto result = [&](int32_t n, int32_t hit) {
-        const bool fr = hit == kNoHit;
-        a.free_out[e] = fr ? 1 : 0;
-        if (a.first_hit) a.first_hit[e] = fr ? -1 : hit;
-        states = fr ? (unsigned long long)n + 1ull : (unsigned long long)hit + 1ull;
-        edges = 1;
-    };
-    edge_flat_team<KIND, OT, OBS>(sc, lds, a.E, e, G, TW, a.flat_w0, pool ? kFlatPoolLimit : INT32_MAX, rows,
-                                  [&](int64_t, int32_t n, int32_t hit, int32_t lo) {
-                                      if (pool && hit == kNoHit && lo <= n) {
-                                          n_left = n;
-                                          s_left[atomicAdd(&s_cnt, 1)] = make_int2(team * kFlatMaxEdges + lane, lo);
-                                      } else {
-                                          result(n, hit);
-                                      }
-                                  });
-    if (pool) {
-        __syncthreads();
-        const int R = uniform(s_cnt);
-        auto edge_of = [&](int id, int32_t *&s_hit) {
-            float4 *row = lds + sc.lds_f4 + (id / kFlatMaxEdges) * flat_team_f4(G);
-            const int i = id % kFlatMaxEdges;
-            s_hit = reinterpret_cast<int32_t *>(row + 4 * G) + G + i;
-            return row + 4 * i;
-        };
-        for (int r = 0; r < R; ++r) {
-            const int2 it = s_left[r];
-            int32_t *s_hit;
-            const float4 *row = edge_of(uniform(it.x), s_hit);
-            const int n = uniform(s_hit[-G]);
-            const float4 a0 = row[0], a1 = row[1], b0 = row[2], b1 = row[3];
-            const float A[kMaxDof + 1] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-            const float B[kMaxDof + 1] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-            for (int base = uniform(it.y) + 64 * ((wv + r) % nwv); base <= n; base += 64 * nwv) {
-                if (uniform(__atomic_load_n(s_hit, __ATOMIC_RELAXED)) < base) break;
-                const int j = base + lane;
-                float q[kMaxDof];
-                float t;
-                edge_state(A, B, min(j, n), n, q, t);
-                const bool hit = state_hits<KIND, OT, OBS, true>(sc, lds, q, t, j <= n, ~0ull, (1ull << lane) - 1ull);
-                const uint64_t hm = __ballot(hit && j <= n);
-                if (hm) {
-                    if (lane == 0) atomicMin(s_hit, base + (int)__builtin_ctzll(hm));
-                    break;
-                }
-            }
-        }
-        __syncthreads();
-        if (n_left >= 0) {
-            int32_t *s_hit;
-            (void)edge_of(team * kFlatMaxEdges + lane, s_hit);
-            result(n_left, *s_hit);
-        }
-    }
+    edge_flat_team<KIND, OT, OBS, POOL>(a.sc, lds, a.E, e, G, TW, a.flat_w0, POOL ? 1 : INT32_MAX, rows,
+                                        [&](int64_t, int32_t n, int32_t hit, int32_t) {
+                                            const bool fr = hit == kNoHit;
+                                            a.free_out[e] = fr ? 1 : 0;
+                                            if (a.first_hit) a.first_hit[e] = fr ? -1 : hit;
+                                            states = (unsigned long long)(fr ? n : hit) + 1ull;
+                                            edges = 1;
+                                        });
     if (a.work && wv == team * TW) {
         for (int o = 32; o > 0; o >>= 1) {
             states += __shfl_down(states, o, 64);
@@ -314,17 +291,31 @@ inline void flat_set(EdgeArgs &a, int G, int team, int waves, int w0) {
     a.flat_w0 = std::min(kFlatMaxWidth, std::max(1, w0 * team / G));
 }
 
-// st_check_edges: a wave takes one edge from 1025 edges on (the device has 1024
-// SIMDs), more as the launch grows (E / 3072, up to 32); below that 2, 4 or 8
-// waves share an edge.  100 bridge-length edges of the 6-DOF arm: 12.8 us with
-// eight waves per edge, 16.5 with one, 30 for the chunked plan / items / finish
-// kernels; 4096 extension edges: 24.5 us with 2 edges per wave, 34 with 8, 39
-// chunked; 262144 bridge-length edges of the 7-DOF arm: 665 us with 32 edges,
-// 740 with 8, 2970 chunked.
+// st_check_edges.  Up to 8192 edges a block per CU with the whole block as the
+// team, E / 256 edges each: of eight waves up to 512 edges, where more waves only
+// add to the staging (512 extension edges of the 6-DOF arm 11.4 us, 12.8 with
+// twelve), of twelve from there on, three per SIMD (8318 bridge-length edges of
+// the 7-DOF arm 110 us, 135 with eight).  Above, a wave takes E / 3072 edges (up
+// to 32) and the block pools what its first phase leaves; blocks of twelve
+// waves, still one per CU, up to 49152 edges (20000 as above: 204 us, 235 with
+// four), of four above, as more than one round of blocks balances better with
+// small ones (2^18: 1650 us, 1850 with twelve).
+// First phases of one state per lane, and of a state and a half where that takes
+// long edges of a few per block (513 as above: 26 us, 37) or extension edges (up
+// to 96 states: 3000 of the 7-DOF arm 35 us, 40) in one phase; elsewhere a wider
+// one only adds states past a hit (2000 bridge-length edges 51 us, 58).
 inline void flat_shape_api(EdgeArgs &a) {
-    const int team = a.E <= 256 ? 8 : (a.E <= 512 ? 4 : (a.E <= 1024 ? 2 : 1));
-    const int G = (int)std::max<int64_t>(1, std::min<int64_t>(32, (a.E + 3071) / 3072));
-    flat_set(a, G, team, team == 1 ? 4 : team, 64);
+    if (a.E <= 256) {
+        flat_set(a, 1, 8, 8, 64);
+    } else if (a.E <= 8192) {
+        const int waves = a.E <= 512 ? 8 : kFlatApiWaves, G = (int)((a.E + 255) / 256);
+        flat_set(a, G, waves, waves, 64);
+        const int more = a.flat_w0 + a.flat_w0 / 2;
+        if (G <= 3) a.flat_w0 = more;
+        else if (more >= 72) a.flat_w0 = std::max(a.flat_w0, std::min(more, 96));
+    } else {
+        flat_set(a, (int)std::min<int64_t>(32, (a.E + 3071) / 3072), 1, a.E <= 49152 ? kFlatApiWaves : 4, 64);
+    }
 }
 
 // Extension edges of one problem: 4 x `number` edges (16 by default) per block
@@ -384,6 +375,8 @@ inline int64_t flat_blocks(const EdgeArgs &a) {
     const int64_t per = (int64_t)a.flat * (a.flat_waves / a.flat_team);
     return (a.E + per - 1) / per;
 }
-inline size_t flat_lds_bytes(const EdgeArgs &a) { return flat_lds_bytes(a.flat_waves, a.flat_team, a.flat); }
+inline size_t flat_lds_bytes(const EdgeArgs &a) {
+    return flat_lds_bytes(a.flat_waves, a.flat_team, a.flat, a.flat_team == 1);
+}
 
 }  // namespace st

@@ -1364,7 +1364,7 @@ __global__ __launch_bounds__(64 * kFlatWaves) void k_bridge_check(BridgeArgs a0,
     const int i0 = bx * G, cnt = min(G, nsel - i0);
     // the candidates of edge g: `sub` lanes each (a power of two), all groups
     // of lanes at once; the result goes to the LDS word of the edge
-    uint32_t *s_best = reinterpret_cast<uint32_t *>(lds + sc.lds_f4 + flat_team_f4(G)) + 64 * waves;
+    uint32_t *s_best = reinterpret_cast<uint32_t *>(lds + sc.lds_f4) + flat_words(G, waves, false);
     const int ny0 = uniform(k.bcnt[kBcntBridge + 4]), ny1 = uniform(k.bcnt[kBcntBridge + 5]);  // slices of the two scans
     int sub = 1;
     while (sub < 64 && sub < max(nb0 > 0 ? ny0 : 0, nb1 > 0 ? ny1 : 0)) sub *= 2;
@@ -1399,7 +1399,7 @@ __global__ __launch_bounds__(64 * kFlatWaves) void k_bridge_check(BridgeArgs a0,
     const int64_t i = i0 + lane;
     const bool in = wv == 0 && lane < cnt;
     const int64_t w = in ? (i < nb0 ? k.border_br[i] : k.border_br[a.B + (i - nb0)]) : 0;
-    edge_flat_team<KIND, OT, OBS>(
+    edge_flat_team<KIND, OT, OBS, false>(
         sc, lds, nsel, i, G, waves, max(1, a.w0 * waves / G), a.limit,
         [&](int64_t, float (&A)[kMaxDof + 1], float (&B)[kMaxDof + 1]) {
             const uint32_t bi = s_best[lane];
