@@ -104,10 +104,9 @@ static int batch_build(st_batch *b) {
     BatchLaunch &L = b->L;
     L.P = P;
     if (P == 0) return ST_OK;
-    // node slices per scan tile at most (the device uses what the sets need): a
-    // few thousand scan blocks in total over about a tile per 256 workers and a
-    // partial one per node set, at least 8 slices each so that a member's large
-    // tree is never scanned by a single block
+    // node slices per scan tile at most (the device uses what the sets need and
+    // the launch's blocks hold, see member_scan_blocks): a few thousand scan blocks
+    // in total over about a tile per 256 workers and a partial one per node set
     int64_t tiles = 0;
     for (st_problem *p : b->mem) tiles += (p->prm.batch + 255) / 256 + 2;
     const int nch = (int)std::min<int64_t>(64, std::max<int64_t>(8, 8192 / std::max<int64_t>(tiles, 1)));
@@ -136,6 +135,7 @@ static int batch_build(st_batch *b) {
     int64_t B_max = 0;
     for (st_problem *p : b->mem) B_max = std::max<int64_t>(B_max, p->prm.batch);
     L.scan_tq = B_max <= 64 ? 64 : 256;
+    L.scan_blocks = member_scan_blocks(P, B_max);
     for (int m = 0; m < P; ++m) {
         st_problem *p = b->mem[m];
         const int64_t B = p->prm.batch;

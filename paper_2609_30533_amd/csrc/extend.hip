@@ -366,11 +366,20 @@ constexpr int kMinSliceNodes = 64;  // nearest-node scans: nodes per slice at le
 // 16 or 32 nodes, 87 with 64, 95 with 128, 139 with 512).
 constexpr int kBridgeSliceNodes = 32;
 // Blocks of the bucketed scans at most (7-DOF arm at 8192 samples, five problems:
-// 134-298 us per iteration with 4096, 134-306 with 2048; a batch member: mixed
-// batch of 128, three batches: 224-258 us with 96 blocks, 222-260 with 64, 235-321
-// with 16).
-constexpr int kScanBlocks = 4096, kBridgeScanBlocks = 1024, kMemberScanBlocks = 96;
-
+// 134-298 us per iteration with 4096, 134-306 with 2048).
+constexpr int kScanBlocks = 4096, kBridgeScanBlocks = 1024;
+// The members of a batch share kBatchScanBlocks, a block per eight of the largest
+// member's samples each at most and kMemberScanBlocks at least (mixed batch of 128,
+// three batches: 224-258 us with 96 blocks per member, 222-260 with 64, 235-321 with
+// 16).  With 96 whatever the number and size of the members, a few large ones had
+// one or a few slices per tile: one 7-DOF member of 8192 samples 1540 us per
+// iteration, 366 so, four 6-DOF ones of 4096 666 and 404.  More blocks for members of
+// a few hundred samples only start and leave (40 mixed ones with 300 each 3 % slower).
+constexpr int kBatchScanBlocks = 12288, kMemberScanBlocks = 96, kSamplesPerScanBlock = 8;
+int member_scan_blocks(int members, int64_t samples) {
+    return (int)std::max<int64_t>(kMemberScanBlocks,
+                                  std::min<int64_t>(kBatchScanBlocks / members, samples / kSamplesPerScanBlock));
+}
 
 // ---------------------------------------------------------------------------
 // Large node sets: matrix-core filter, exact test of what passes it.
@@ -2278,8 +2287,9 @@ int launch_batch_iteration(const BatchLaunch &L, hipStream_t s) {
     ST_HIP(hipGetLastError());
     auto scan_multi = [&](auto mode, auto tq, auto filter, int mt, int n, const int32_t *members,
                           const ScanArgs *args) {
+        const int blocks = decltype(mode)::value == kScanBridge ? std::min(L.scan_blocks, kBridgeScanBlocks) : L.scan_blocks;
         k_scan<decltype(mode)::value, true, decltype(tq)::value, decltype(filter)::value>
-            <<<dim3(scan_grid(mt, L.nch, kMemberScanBlocks), 1, n), decltype(tq)::value, 0, s>>>(ScanArgs{}, args, members);
+            <<<dim3(scan_grid(mt, L.nch, blocks), 1, n), decltype(tq)::value, 0, s>>>(ScanArgs{}, args, members);
     };
     auto scan_launch = [&](auto mode, int mt, int n, const int32_t *members, const ScanArgs *args) {
         constexpr bool near = decltype(mode)::value != kScanBridge;

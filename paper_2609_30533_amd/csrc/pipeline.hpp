@@ -172,6 +172,7 @@ struct BatchLaunch {
     int mt_nn_ir = 0, mt_nn_rr = 0, mt_br = 0, nch = 1, nb_worker = 0, nb_edge = 0, max_pools = 0;
     int ins_threads = 64;  // insertion block size for the largest member
     int scan_tq = 256;     // queries per scan tile and scan block size (256 or 64)
+    int scan_blocks = 96;  // blocks of a member's scans at most (a tile each at least)
     bool filter = false;   // a member's nearest-node scan may reach the filter
     bool ext_flat = true;  // every member's extension edges take the flattened path
     std::vector<BatchClass> classes;
@@ -186,5 +187,7 @@ size_t scene_lds_bytes(const SceneDev &sc);
 // windows lo, hi, cum as doubles when they fit.
 size_t sample_lds_bytes(const st_problem *p, int32_t *nw_lds);
 bool scan_may_filter(int64_t queries, int64_t nodes);
+// Scan blocks per member of a batch whose largest member draws `samples`.
+int member_scan_blocks(int members, int64_t samples);
 
 }  // namespace st
