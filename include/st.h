@@ -454,7 +454,8 @@ int st_proposal_set(st_problem *p, const float *z, float mix, void *stream);
  * st_check_edges (powers of two up to 64; 0 keeps; choosing lanes for
  * st_check_edges puts it on the chunked path, which keeps work buffers in the
  * handle: its calls on one handle must not overlap, and one that is captured
- * needs an earlier call of its size; the lanes of bridge edges are kept and reported, but their check lays states
+ * needs an earlier call of its size; st_set_state_split with -1 takes it back
+ * to the one-kernel path; the lanes of bridge edges are kept and reported, but their check lays states
  * end to end and has no chunks).  Results do not depend on these.
  * Synchronous; drops captured iteration graphs. */
 int st_set_tuning(st_problem *p, int32_t obstacle_tile, int32_t lanes_extension, int32_t lanes_bridge,
@@ -466,7 +467,7 @@ int st_set_tuning(st_problem *p, int32_t obstacle_tile, int32_t lanes_extension,
  * to fill the device, more instructions per state) for extension edges,
  * bridge edges and st_check_edges; -1 chooses by launch size (4 up to 256
  * edges, else 1; a batch counts the edges of all its members; st_check_edges:
- * the one-kernel path); 0 keeps.  Bridge edges always choose by what a phase
+ * the one-kernel path again, whatever lanes were chosen before); 0 keeps.  Bridge edges always choose by what a phase
  * of their check leaves free.  A translating robot always uses
  * one lane per state.  Results do not depend on these.  Synchronous; drops
  * captured iteration graphs. */

@@ -649,6 +649,7 @@ int st_set_state_split(st_problem *p, int32_t split_extension, int32_t split_bri
     p->split_ext = se;
     p->split_api = sk;
     if (split_check != 0) p->api_split = sk >= 0;
+    if (split_check == -1) p->api_lanes = false;
     ST_HIP(hipDeviceSynchronize());
     graphs_free(p);
     return ST_OK;

@@ -209,7 +209,8 @@ struct st_problem {
     int tune_ext = 5, tune_br = 4, tune_api = 5;
     // lanes per state (log2) for extension and st_check_edges launches; -1 chooses by size
     int split_ext = -1, split_api = -1;
-    // st_check_edges takes the chunked path when the caller chose its lanes
+    // st_check_edges takes the chunked path once the caller chose its lanes, until
+    // a state split of -1
     bool api_lanes = false, api_split = false;
     // a quarter of the extension edges per block of the one-kernel path (0: chunked item path)
     int flat_ext = 4;
