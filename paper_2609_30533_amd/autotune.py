@@ -1,15 +1,14 @@
-"""Autotuner of the many-problem launch: samples per problem per iteration
-and lanes per bridge chunk, chosen per problem class and cached as JSON.
+"""Autotuner of the many-problem launch: samples per problem per iteration,
+chosen per problem class and cached as JSON.
 
 A class is (degrees of freedom, obstacle-count bucket).  For each class the
 tuner draws tuning problems of that class (seeds disjoint from evaluation
-seeds), plans them as one batch under each candidate setting for a fixed
-device-time budget, and scores a setting by the summed time to first
-solution (an unsolved problem counts the whole budget).  It searches the
-sample count first with 16 lanes per bridge chunk, then the lane count at
-the best sample count.  (Extension edges take the flattened path, where the
-lanes per chunk play no part.)  Everything it runs is the library's planner;
-this module only orders the experiments and keeps the table.
+seeds), plans them as one batch under each candidate sample count for a fixed
+device-time budget, and scores it by the summed time to first solution (an
+unsolved problem counts the whole budget).  The lanes per edge chunk that the
+table also holds are not searched: extension and bridge edges are checked end
+to end, without chunks.  Everything it runs is the library's planner; this
+module only orders the experiments and keeps the table.
 """
 from __future__ import annotations
 
@@ -25,7 +24,7 @@ from . import scenes
 from .lib import Batch, Problem
 
 SAMPLES = (64, 128, 256, 512)
-LANES = (8, 16, 32, 64)
+LANES = (8, 16, 32, 64)  # a table's lanes per bridge chunk are one of these
 LANES_FIRST = 16
 OBS_BUCKETS = (8, 16, 32, 64)
 TUNE_SEED0 = 3_000_000
@@ -89,17 +88,10 @@ def tune(keys, n_problems=48, budget_ms=400.0, log=print):
         best = None
         for smp in SAMPLES:
             sc, ns = score(probs, smp, LANES_FIRST, budget_ms)
-            log("[tune] %s samples %d bridge lanes %d: score %.1f solved %d" % (key, smp, LANES_FIRST, sc, ns))
+            log("[tune] %s samples %d: score %.1f solved %d" % (key, smp, sc, ns))
             if best is None or sc < best[0]:
-                best = (sc, smp, LANES_FIRST)
-        for ln in LANES:
-            if ln == LANES_FIRST:
-                continue
-            sc, ns = score(probs, best[1], ln, budget_ms)
-            log("[tune] %s samples %d bridge lanes %d: score %.1f solved %d" % (key, best[1], ln, sc, ns))
-            if sc < best[0]:
-                best = (sc, best[1], ln)
-        table[key] = {"samples": best[1], "lanes_extension": DEFAULT["lanes_extension"], "lanes_bridge": best[2],
+                best = (sc, smp)
+        table[key] = {"samples": best[1], "lanes_extension": DEFAULT["lanes_extension"], "lanes_bridge": LANES_FIRST,
                       "score": best[0]}
     return table
 
@@ -114,7 +106,7 @@ def load(path):
 
 
 def main(argv=None):
-    ap = argparse.ArgumentParser(description="tune samples per problem and lanes per edge for batched launches")
+    ap = argparse.ArgumentParser(description="tune samples per problem for batched launches")
     ap.add_argument("--out", required=True)
     ap.add_argument("--problems", type=int, default=48)
     ap.add_argument("--budget-ms", type=float, default=400.0)
