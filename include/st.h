@@ -243,8 +243,8 @@ int st_check_edges(st_problem *p, int64_t E, const float *xa, const float *xb, u
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * check and results; the call allocates nothing (host or device) and keeps no
  * work area, so calls on different streams or threads are independent.
- * E <= ST_NOALLOC_MAX_EDGES, else ST_EINVAL.  Inputs and outputs as for
- * st_check_edges.  Async on stream. */
+ * E <= ST_NOALLOC_MAX_EDGES, else ST_EINVAL (the size of a work area that the
+ * call once had).  Inputs and outputs as for st_check_edges.  Async on stream. */
 #define ST_NOALLOC_MAX_EDGES 65536
 int st_check_edges_noalloc(st_problem *p, int64_t E, const float *xa, const float *xb, uint8_t *free_out,
                            int32_t *first_hit, void *stream);
@@ -480,7 +480,7 @@ int st_set_state_split(st_problem *p, int32_t split_extension, int32_t split_bri
  * their states end to end and deals them to its waves in rounds of 64.
  * 0 selects the chunked path.  Results do not depend on
  * this.  Default 4.  In a batch (st_batch_create) a member on this path takes
- * 8 edges per block of four waves.
+ * 4 to 16 edges per block of four waves, by the edges of the whole launch.
  * Synchronous; drops captured graphs. */
 int st_set_flat_extension(st_problem *p, int32_t edges_per_block);
 

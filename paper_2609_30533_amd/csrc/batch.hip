@@ -272,8 +272,8 @@ int st_batch_create(st_problem *const *problems, int32_t n, int32_t iters_per_la
             set_error("st_batch_create: problem %d is null or repeated", i);
             return ST_EINVAL;
         }
-        // a member's samples index the second grid dimension of the batched
-        // bridge check (one block each)
+        // a documented limit: with it every grid dimension that a member's samples
+        // decide stays within the launch limits
         if (problems[i]->prm.batch > kBatchMaxSamples) {
             set_error("st_batch_create: problem %d draws %d samples per iteration (at most %d in a batch)", i,
                       (int)problems[i]->prm.batch, kBatchMaxSamples);

@@ -27,8 +27,7 @@ __global__ __launch_bounds__(256) void k_check_states(SceneDev sc, int64_t M, co
 #pragma unroll
         for (int j = 0; j < kMaxDof; ++j) q[j] = (act && j < sc.d) ? x[i * w + j] : 0.f;
         if (act) t = x[i * w + sc.d];
-        const uint64_t self = 1ull << lane;
-        const bool hit = state_hits<KIND, OT, OBS, true>(sc, lds, q, t, act, self, 0ull);
+        const bool hit = state_hits<KIND, OT, OBS>(sc, lds, q, t, act, 0ull);
         if (act) free_out[i] = hit ? 0 : 1;
     }
 }
@@ -307,7 +306,7 @@ __device__ __forceinline__ void edge_items_body(const EdgeArgs &a, float4 *lds, 
 #pragma unroll
                 for (int k = 0; k < kMaxDof; ++k) q[k] = 0.f;
             }
-            const bool hit = state_hits<KIND, OT, OBS, true, SPLIT>(sc, lds, q, t, act, group_mask, lower_mask, part);
+            const bool hit = state_hits<KIND, OT, OBS, SPLIT>(sc, lds, q, t, act, lower_mask, part);
             const uint64_t hm = __ballot(hit && act) & group_mask;
             if (!done && hm) {
                 // one atomic per group: its lowest hitting lane

@@ -90,8 +90,8 @@ __device__ __forceinline__ void edge_state(const float (&A)[kMaxDof + 1], const 
 // (arms only), which shortens the chain of the narrow phases.
 //
 // A lane skips a state above a hit already found for its edge; within a round
-// the lanes of one edge form the group of the FIRST rule, and hits merge with
-// an atomic minimum; phases run in state order, so the least colliding index
+// the lanes of one edge form a group of state_hits, and hits merge with an atomic
+// minimum; phases run in state order, so the least colliding index
 // is exact.
 // ---------------------------------------------------------------------------
 
@@ -226,7 +226,7 @@ __device__ __forceinline__ void edge_flat_team(const SceneDev &sc, float4 *lds, 
             const int g = base + (lane >> shift), j = __shfl(lo, k, 64) + g - o0;
             // a state above a known hit of its edge is not needed
             const bool act = g < T && j <= __atomic_load_n(&s_hit[i], __ATOMIC_RELAXED);
-            // the lanes of lower states of this edge in this round (FIRST rule)
+            // the lanes of lower states of this edge in this round
             const uint64_t lower = ((1ull << (lane - part)) - 1ull) & ~((1ull << (max(o0 - base, 0) << shift)) - 1ull);
             const float4 a0 = s_row[4 * i], a1 = s_row[4 * i + 1], b0 = s_row[4 * i + 2], b1 = s_row[4 * i + 3];
             const float A[kMaxDof + 1] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
@@ -234,8 +234,8 @@ __device__ __forceinline__ void edge_flat_team(const SceneDev &sc, float4 *lds, 
             float q[kMaxDof];
             float t;
             edge_state(A, B, j, n, q, t);
-            const bool hit = state_hits<KIND, OT, OBS, true, KIND == kTranslate ? 1 : kSplitAny>(
-                sc, lds, q, t, act, 0ull, lower, part, shift);
+            const bool hit =
+                state_hits<KIND, OT, OBS, KIND == kTranslate ? 1 : kSplitAny>(sc, lds, q, t, act, lower, part, shift);
             if (hit && act && part == 0) atomicMin(&s_hit[i], j);
         }
         if (W > 1) __syncthreads();

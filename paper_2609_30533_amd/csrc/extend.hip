@@ -392,11 +392,15 @@ int member_scan_blocks(int members, int64_t samples) {
 // the tile can still improve its query.  Only those pairs are evaluated, with
 // the plain scan's own arithmetic, so the results are the same bit for bit.
 //
-// Bound.  With x = xh + xl + r, xh = bf16(x), xl = bf16(x - xh) and |r| <=
-// 2^-18 |x|, the sum  |x|^2 + |q|^2 - 2 (qh xh + qh xl + ql xh)  in FP32 differs
-// from |x - q|^2 by less than 2^-15.7 (|x|^2 + |q|^2): 3 2^-18 2 |x||q| from the
-// products left out and 27 additions of partial sums below 2 (|x|^2 + |q|^2).
-// Using (1 - eps) |x|^2 and (1 - eps) |q|^2, eps = 2^-14, makes it a lower bound.
+// Bound.  With x = xh + xl + r, xh = bf16(x), xl = bf16(x - xh): |xl| <= 2^-8 |x|
+// and |r| <= 2^-17 |x|.  Of a coordinate's product x q the three terms qh xh + qh
+// xl + ql xh leave out ql xl (2^-16 |x||q|) and x and q times the other's r (2^-17
+// each), together 2^-15 |x||q|; doubled and summed at most 2^-15 (|x|^2 + |q|^2).
+// The 27 additions of partial sums below 2 (|x|^2 + |q|^2) add 2^-17.2 of it even
+// if each cuts its last bit off, the squares and the exact test's own roundings
+// 2^-19: the sum  |x|^2 + |q|^2 - 2 (qh xh + qh xl + ql xh)  in FP32 differs from
+// |x - q|^2 by less than 2^-14.6 (|x|^2 + |q|^2).  Using (1 - eps) |x|^2 and (1 -
+// eps) |q|^2, eps = 2^-14, makes it a lower bound with a factor 1.5 in hand.
 // The squares travel as three bf16 parts each, so one operand row is 27 of 32
 // places: 3 per coordinate, 3 for the node's square, 3 for the query's constant
 // (which multiply ones).  rho (Eq. 7) asks for D2 <= w2 and D2 + w2 <= best with
@@ -1489,7 +1493,7 @@ __global__ __launch_bounds__(64 * kFlatWaves) void k_bridge_rest(BridgeArgs a) {
             float q[kMaxDof];
             float t;
             edge_state(A, B, min(j, n), n, q, t);
-            const bool hit = state_hits<KIND, OT, OBS, true>(sc, lds, q, t, j <= n, ~0ull, (1ull << lane) - 1ull);
+            const bool hit = state_hits<KIND, OT, OBS>(sc, lds, q, t, j <= n, (1ull << lane) - 1ull);
             const uint64_t hm = __ballot(hit && j <= n);
             if (hm) {
                 if (lane == 0) atomicMin(&a.hit[w], base + (int)__builtin_ctzll(hm));

@@ -152,7 +152,8 @@ struct BatchClass {
     size_t lds_sample;      // the sampler's (scene and guided windows), maximum over the members
 };
 
-// Samples per iteration of a batch member at most (a grid dimension).
+// Samples per iteration of a batch member at most (documented; every grid
+// dimension that they decide stays within the launch limits).
 constexpr int kBatchMaxSamples = 65535;
 
 // Device arrays of records (P problems) and grid maxima for one iteration of

@@ -12,9 +12,9 @@
 //           cost[total], rootT[total]; pool p occupies [base(p), base(p)+cap(p)).
 //
 // The collision test keeps one space-time state per lane.  Forward kinematics
-// runs in registers with the DH constants from the kernel arguments; sphere
-// offsets are staged in LDS and read as broadcasts; obstacle centres at the
-// lane's own time come from the segment table, also staged in LDS.  A pair
+// runs in registers; the DH constants and the sphere offsets are staged in LDS
+// and read as broadcasts; obstacle centres at the lane's own time come from the
+// segment table, also staged in LDS.  A pair
 // collides iff |c - o| < r_s + r_o + eps, evaluated in expanded form as a
 // minimum over the obstacle tile (sphere_clear).
 #pragma once
@@ -337,10 +337,10 @@ __device__ __forceinline__ float next_angle(float (&q)[kMaxDof]) {
 // registers, which took a fully unrolled chain of 10000 instructions.
 // Updates hit / hm / alive as the obstacle tiles do.  Every lane of the wave
 // must call this.
-template <bool FIRST, int SPLIT>
+template <int SPLIT>
 __device__ __forceinline__ void static_pass(const SceneDev &sc, const float4 *lds, const float *q, bool &alive,
-                                            bool &hit, uint64_t &hm, uint64_t group_mask, uint64_t lower_mask,
-                                            int part, int st_lane, int step) {
+                                            bool &hit, uint64_t &hm, uint64_t lower_mask, int part, int st_lane,
+                                            int step) {
     Frame Fa;
     frame_identity(Fa);
     float qa[kMaxDof];  // the joints above link la
@@ -350,8 +350,7 @@ __device__ __forceinline__ void static_pass(const SceneDev &sc, const float4 *ld
         hm |= __ballot(h);
         hit = hit || state_hit<SPLIT>(hm, st_lane, step);
         const uint64_t mk = __ballot(hit);
-        if (FIRST) alive = alive && !hit && !(mk & lower_mask);
-        else alive = alive && !(mk & group_mask);
+        alive = alive && !hit && !(mk & lower_mask);
     };
     LinkRec ra = link_rec(sc, lds, 0);
 #pragma nounroll
@@ -440,16 +439,13 @@ __device__ __forceinline__ bool state_hit(uint64_t hm, int st_lane, int step) {
 // over its lanes, so all SPLIT lanes return the same answer.  This divides
 // the dependent chain of one state check by about SPLIT for launches too
 // small to fill the device.  `alive` enters true for lanes that must check;
-// after every link the wave ballots the hits and each lane decides whether it
-// may stop:
-//   FIRST:  stop on a hit of its state, or when a lower state of its group
-//           has hit (so the least colliding index of a group is exact);
-//           lower_mask holds the lanes of the lower states;
-//   !FIRST: stop as soon as any lane of its group has hit.
+// after every link the wave ballots the hits and a lane stops on a hit of its
+// state, or when a lower state of its group has hit (so the least colliding
+// index of a group is exact); lower_mask holds the lanes of the lower states.
 // Every lane of the wave must call this (it contains ballots).
-template <int KIND, int OT, int OBS, bool FIRST, int SPLIT = 1>
+template <int KIND, int OT, int OBS, int SPLIT = 1>
 __device__ __forceinline__ bool state_hits(const SceneDev &sc, const float4 *lds, const float *q, float t, bool alive,
-                                           uint64_t group_mask, uint64_t lower_mask, int part = 0, int shift = 0) {
+                                           uint64_t lower_mask, int part = 0, int shift = 0) {
     static_assert(SPLIT == kSplitAny || SPLIT == 1 || SPLIT == 2 || SPLIT == 4, "state split");
     const int step = split_step<SPLIT>(shift);
     const int st_lane = lane_id() & ~(step - 1);  // first lane of this state
@@ -470,8 +466,7 @@ __device__ __forceinline__ bool state_hits(const SceneDev &sc, const float4 *lds
     }
     {
         const uint64_t m = __ballot(hit);
-        if (FIRST) alive = alive && !hit && !(m & lower_mask);
-        else alive = alive && !(m & group_mask);
+        alive = alive && !hit && !(m & lower_mask);
     }
     int kseg = 0;
     if (OBS == kObsShared) kseg = shared_segment(sc, lds, t);
@@ -497,8 +492,7 @@ __device__ __forceinline__ bool state_hits(const SceneDev &sc, const float4 *lds
                 hm |= __ballot(alive && dmin < 0.0f);
                 hit = hit || state_hit<SPLIT>(hm, st_lane, step);
                 const uint64_t m = __ballot(hit);
-                if (FIRST) alive = alive && !hit && !(m & lower_mask);
-                else alive = alive && !(m & group_mask);
+                alive = alive && !hit && !(m & lower_mask);
             } else {
                 // world <- link frame.  One link per turn of a loop that is not
                 // unrolled: the unrolled chain was 5000 instructions (40 KB,
@@ -561,8 +555,7 @@ __device__ __forceinline__ bool state_hits(const SceneDev &sc, const float4 *lds
                         hm |= __ballot(alive && dmin < 0.0f);
                         hit = hit || state_hit<SPLIT>(hm, st_lane, step);
                         const uint64_t m = __ballot(hit);
-                        if (FIRST) alive = alive && !hit && !(m & lower_mask);
-                        else alive = alive && !(m & group_mask);
+                        alive = alive && !hit && !(m & lower_mask);
                     }
                 }
             }
@@ -572,7 +565,7 @@ __device__ __forceinline__ bool state_hits(const SceneDev &sc, const float4 *lds
     }
     // time-independent terms for the lanes still undecided
     if (KIND == kDHStatic && __ballot(alive) != 0)
-        static_pass<FIRST, SPLIT>(sc, lds, q, alive, hit, hm, group_mask, lower_mask, part, st_lane, step);
+        static_pass<SPLIT>(sc, lds, q, alive, hit, hm, lower_mask, part, st_lane, step);
     return hit;
 }
 

@@ -262,7 +262,8 @@ inline int split_for(int setting, int64_t E) {
     if (setting >= 0) return setting;
     return E <= 256 ? 2 : 0;
 }
-// Threads of an insertion block (one block per pool): whole waves, enough to look
+// Threads of an insertion block (one per pool, four for a single problem's forward
+// pool): whole waves, enough to look
 // at B workers in one chunk, at most 1024; and its list of a chunk's workers.
 constexpr int kInsWorkers = 8;  // workers per thread and chunk
 inline int insert_threads(int64_t B) {
