@@ -319,12 +319,12 @@ def ttfs_section(lib, args, validate):
         "ttfs_workload": "arm6 evaluation seeds 0..%d with start and goal accepted by the library (%d problems), "
                          "planner seeds %s; plain = one problem at a time, B=4096, %.0f ms budget, stop at the "
                          "first solution; batched = all problems in one batch, B=%d each, %.0f ms; learned and "
-                         "untrained networks mixed 50/50; %s lanes per bridge chunk in both; a time is device "
+                         "untrained networks mixed 50/50; a time is device "
                          "time from the first iteration's launch to the end of the iteration that found the "
                          "first solution, the set-up (start check, graph capture, proposal) excluded on both "
                          "sides" % (
                              args.ttfs_problems - 1, n, list(args.planner_seeds), args.ttfs_single_ms,
-                             args.ttfs_batch_samples, args.ttfs_ms, args.ttfs_lanes_bridge or "default"),
+                             args.ttfs_batch_samples, args.ttfs_ms),
         "ttfs_problems": n,
         "ttfs_runs": n * len(args.planner_seeds),
     }
@@ -488,8 +488,10 @@ def edge_sweep(lib, scenes, n_edges, reps=5):
     W = flops_per_state(prob)
     out = []
     for ot in (8, 16):
-        for lanes in (16, 32, 64):
+        for lanes in (0, 16, 32, 64):  # 0: the one-kernel check, which a call takes without chosen lanes
             gp.set_tuning(obstacle_tile=ot, lanes_check=lanes)
+            if lanes == 0:
+                gp.set_state_split(check=-1)
             free, fh = gp.check_edges(da, db)
             torch.cuda.synchronize()
             fh = fh.cpu().numpy()
@@ -777,8 +779,8 @@ def main():
     ap.add_argument("--batch-obstacle-tile", type=int, default=16,
                     help="obstacle tile forced on every member of the heterogeneous batch (0: each its own)")
     ap.add_argument("--ttfs-lanes-bridge", type=int, default=32,
-                    help="lanes per bridge chunk of every time-to-first-solution problem, plain and batched "
-                         "(0: the library's default)")
+                    help="lanes per bridge chunk of every time-to-first-solution problem, plain and batched (0: the "
+                         "library's default); kept by the library, but bridge edges have no chunks: no effect")
     ap.add_argument("--ttfs-batch-samples", type=int, default=32,
                     help="samples per iteration of each problem in the time-to-first-solution batches")
     ap.add_argument("--no-cpu-baseline", action="store_true")
