@@ -509,9 +509,15 @@ static int build_fresh_state(st_problem *p) {
     return dev_upload(&p->d_start, start, kMaxDof + 1);
 }
 
+// The kernel runs on the problem's own device, whichever is current.
 static int init_state(st_problem *p) {
-    ST_HIP(launch_init_state(p));
-    ST_HIP(hipStreamSynchronize(nullptr));
+    int cur = p->device;
+    ST_HIP(hipGetDevice(&cur));
+    if (cur != p->device) ST_HIP(hipSetDevice(p->device));
+    hipError_t e = launch_init_state(p);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (cur != p->device) (void)hipSetDevice(cur);
+    if (e != hipSuccess) return fail(ST_EHIP, "planner state reset failed: %s", hipGetErrorString(e));
     p->iter = 0;
     p->nodes_known = p->tree.n_pools;
     p->nodes_iter = 0;
